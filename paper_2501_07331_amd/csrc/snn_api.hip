@@ -68,7 +68,14 @@ struct snn_net {
     int read_threads;           // readout workgroup size
     size_t lds_core_f, lds_core_b, lds_scan, lds_read, lds_grad, lds_radj;
     int mask_off, ids_off, scan_tb, table_lds;
-    int bpart_off;              // backward-core LDS plan
+    int bpart_off;              // backward-core LDS plan: partial jump sums or jump slots
+    int split_H;                // helper waves of the split backward core (0: not used)
+    int split_run;              // steps that its waves may run past a step's ring row
+    uint2* near;                // its synapses of slot 0 (see CoreBwdArgs)
+    int* ncnt;
+    int* act;
+    uint2* far;                 // its far table, every projection
+    JumpData* jump;             // [n_lif][B][cap]
     int bring_mode[SNN_MAX_LAYERS];   // adjoint ring of a LIF layer: -2 none, -1 HBM, >= 0 LDS
                                       // byte offset
     int radj_threads, radj_tab;
@@ -103,6 +110,7 @@ struct snn_net {
     float* rec_I;
     int* rec_idx;
     int* rec_cnt;
+    unsigned long long* masks;  // [n_lif][B][T][core waves] spike masks
     int* rec_goff;
     unsigned short* rec_gstep;
     float* z;
@@ -165,7 +173,8 @@ static void free_all(snn_net* n) {
                     n->src,     n->Vf,      n->If,       n->table,     n->tr_lif, n->tr_out,
                     n->A2,       n->in_goff,   n->in_gstep, n->st,
                     n->gpart,   n->ws,      n->steptab, n->mom,   n->xlp_out, n->ncount,
-                    n->nterm,   n->clx};
+                    n->nterm,   n->clx,     n->masks, n->near, n->ncnt, n->act,
+                    n->far,     n->jump};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     for (int p = 0; p < SNN_MAXP; ++p)
@@ -326,9 +335,10 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
     }
     net->reg_nu = (double)opts->reg_target;
     for (int l = 0; l < n_layers; ++l) t.Sb[l] = 0;
+    // (at least two rows: a step's row is read while the next one is written)
     for (int p = 0; p < t.P; ++p)
         if (t.pre[p] != 0 && t.kind[t.post[p]] == SNN_LIF)
-            t.Sb[t.post[p]] = std::max(t.Sb[t.post[p]], t.Sp[p]);
+            t.Sb[t.post[p]] = std::max(t.Sb[t.post[p]], std::max(t.Sp[p], 2));
 
     // ---- LDS plans (the kernels' LDS limits first: occupancy depends on them)
     {
@@ -342,6 +352,10 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         if (e == hipSuccess) {
             what = "backward LDS limits";
             e = set_backward_lds_limits(kLds, &bad);
+        }
+        if (e == hipSuccess) {
+            what = "split backward core LDS limits";
+            e = set_split_lds_limits(kLds, &bad);
         }
         if (e != hipSuccess) {
             snprintf(g_create_err, sizeof(g_create_err), "snn_create: %s (kernel %d): %s", what, bad,
@@ -446,7 +460,13 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         const int NL = std::max(t.n_lif, 1);
         const int KP = bwd_prefetch(NL);
         net->bpart_off = 0;
-        const size_t part = align16((size_t)2 * NL * KP * 4 * nwaves * sizeof(double));
+        // the split core (neuron waves and up to 12 helper waves) wherever the
+        // layers leave room for at least four helpers and have LIF -> LIF
+        // projections; its jump slots take the place of the partial sums
+        const int H = std::min(12, 16 - nwaves);
+        const bool split = !hbm && net->cl_np > 0 && H >= 4 && backward_split_serves(t.n_lif, net->cl_np, maxlif);
+        const size_t part = split ? align16((size_t)2 * t.lif_total * sizeof(JumpData))
+                                  : align16((size_t)2 * NL * KP * 4 * nwaves * sizeof(double));
         size_t used = part;
         bool all_lds = !hbm;
         for (int l = 0; l < n_layers; ++l) {
@@ -491,6 +511,12 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
                 for (int l = 0; l < n_layers; ++l) net->bring_mode[l] = mode[l];
                 used = u;
             }
+        }
+        if (split && all_lds && !net->cl_b) {
+            net->split_H = H;
+            net->split_run = t.T;
+            for (int l = 0; l < n_layers; ++l)
+                if (read_by_lif[l]) net->split_run = std::min(net->split_run, t.Sb[l] - 1);
         }
         for (int l = 0; l < n_layers; ++l) t.bring[l] = net->bring_mode[l] >= 0 ? net->bring_mode[l] : -1;
         net->lds_core_b = used;
@@ -643,6 +669,14 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
     ALLOC(net->rec_I, nl * B * cap);
     ALLOC(net->rec_idx, nl * B * T1);
     ALLOC(net->rec_cnt, nl * B);
+    if (net->split_H > 0) {
+        ALLOC(net->near, (size_t)t.lif_total * kNearCap);
+        ALLOC(net->ncnt, (size_t)t.lif_total + 1);
+        ALLOC(net->act, B * T + B);
+        ALLOC(net->far, (size_t)net->n_params);
+        ALLOC(net->jump, nl * B * cap);
+    }
+    ALLOC(net->masks, nl * B * T * (size_t)nwaves);
     ALLOC(net->rec_goff, nl * B * (t.maxn + 1));
     // (per layer a multiple of 8 entries, so that every layer starts 16-byte
     // aligned, and slack: the gradient pass copies the 16-bit lists as dwords)
@@ -902,6 +936,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             y.rec_idx = net->rec_idx + li * B * (size_t)(t.T + 1);
             y.rec_cnt = net->rec_cnt + li * B;
             y.steptab = net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
+            y.masks = net->masks + li * B * (size_t)t.T * (net->core_threads / 64);
             y.ncount = net->reg_on ? net->ncount + t.lif_off[l] : nullptr;
             y.out_count = records[li].count;
             y.out_step = records[li].step;
@@ -1183,6 +1218,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
                 const int q = t.post[p];
                 if (t.pre[p] != l || t.kind[q] != SNN_LIF) continue;
                 y.ws[y.npost] = net->ws + t.woff[p];
+                y.far[y.npost] = net->far + t.woff[p];
                 y.nq[y.npost] = t.n[q];
                 y.npre[y.npost] = t.n[l];
                 y.qS[y.npost] = t.Sb[q];
@@ -1196,6 +1232,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
                     const int q = t.post[p];
                     if (t.pre[p] == 0 || t.kind[q] != SNN_LIF) continue;
                     y.ws[k] = net->ws + t.woff[p];
+                    y.far[k] = net->far + t.woff[p];
                     y.nq[k] = t.n[q];
                     y.npre[k] = t.n[t.pre[p]];
                     y.qS[k] = t.Sb[q];
@@ -1203,15 +1240,30 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
                     y.qring[k] = net->bring[q];
                 }
             }
+            y.jump = net->jump + li * B * cap;
             y.recI = net->rec_I + li * B * cap;
             y.recn = net->rec_n + li * B * cap;
             y.steptab = net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
+            y.rec_idx = net->rec_idx + li * B * (size_t)(t.T + 1);
+            y.masks = net->masks + li * B * (size_t)t.T * (net->core_threads / 64);
             y.A2 = jump_x[li];
         }
         a.traj = net->tr_lif;
         a.st = net->st;
         a.part_off = net->bpart_off;
-        if (net->cl_b)
+        a.H = net->split_H;
+        a.slot_off = net->bpart_off;
+        a.run_max = net->split_run;
+        a.near = net->near;
+        a.ncnt = net->ncnt;
+        a.nmax = net->ncnt + t.lif_total;
+        a.act = net->act;
+        a.nact = net->act + (size_t)t.B * t.T;
+        if (net->split_H > 0) {
+            HIP_TRY(net, launch_zero_ints(a.nmax, 1, s));
+            HIP_TRY(net, launch_backward_prep(a, t.n_lif, s));
+            TIMED(net, K_BCORE, launch_backward_split(a, t.n_lif, net->cl_np, net->lds_core_b, s));
+        } else if (net->cl_b)
             TIMED(net, K_BCORE, launch_backward_clusters(net, a, s));
         else
             TIMED(net, K_BCORE,

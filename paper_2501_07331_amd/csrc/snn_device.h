@@ -40,13 +40,13 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 template <typename T>
 using gptr = __attribute__((address_space(1))) T*;
 
-// x of the lane given by the DPP control CTRL (within 16-lane rows), fp64 as
-// two 32-bit moves.
-template <int CTRL>
+// x of the lane given by the DPP control CTRL, fp64 as two 32-bit moves; +0 in
+// the rows of 16 lanes that ROWS leaves out.
+template <int CTRL, int ROWS = 0xF>
 __device__ __forceinline__ double dpp_f64(double x) {
     const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, ROWS, 0xF, false);
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 

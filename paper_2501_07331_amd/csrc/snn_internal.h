@@ -116,6 +116,7 @@ struct FwdLayer {
     int* rec_idx;                      // [B][T+1] first record of each step
     int* rec_cnt;                      // [B]
     int* steptab;                      // [B][T][SNN_STEP_ROW]
+    unsigned long long* masks;         // [B][T][NW] spikes of each 64 neurons, one bit each
     int* ncount;                       // [n] spikes per neuron over the batch (added), or NULL
     int* out_count;                    // caller's records: [B], [B][cap], [B][cap]
     int* out_step;
@@ -180,6 +181,17 @@ struct ReadoutBwdArgs {
     int tab_lds;                       // 1: the [T][C] table of lambda_I - lambda_V lives in LDS
 };
 
+// Synapses of slot 0 that a spiking neuron's own lane of the split backward
+// core adds: up to kNearCap per neuron, the first kNearRegs from registers.
+// (Delays drawn from 0 .. 50 give a neuron 2.6 of them among 256 posts.)
+constexpr int kNearRegs = 8, kNearCap = 24;
+
+// A recorded spike's jump lambda_V <- k lambda_V + r A (A: the numerator's sum
+// so far; r < 0: skipped).
+struct JumpData {
+    double A, k, r;
+};
+
 // One LIF layer as seen by the backward core.
 struct BwdLayer {
     int n, lif_off;
@@ -197,9 +209,13 @@ struct BwdLayer {
     int qring_lds[2];                  //   its adjoint ring (LDS byte offset, or -1: global qring)
     double* qring[2];
     const uint2* ws[2];                //   (weight bits, slot) [n][nq]
+    uint2* far[2];                     //   split core: its far table [n][nq]
+    JumpData* jump;                    // split core: [B][cap]
     const float* recI;                 // [B][cap] I- of the records
     const int* recn;                   // [B][cap] neuron of the records
     const int* steptab;                // [B][T][SNN_STEP_ROW] per-step spike table
+    const int* rec_idx;                // [B][T+1] first record of each step
+    const unsigned long long* masks;   // [B][T][NW] spikes of each 64 neurons, one bit each
     const double* A2;                  // [B][cap] extra jump numerator per record (the readout
                                        // part of the jump sums, spike-time loss terms), or NULL
 };
@@ -211,6 +227,16 @@ struct CoreBwdArgs {
     double2* traj;                     // [B][T][lif_total] (lambda_I, lambda_I - lambda_V)
     DevStatus* st;
     int part_off;                      // LDS byte offset of the partial jump sums
+    // split core: helper waves, LDS byte offset of the jump slots
+    // ([2][lif_total] JumpData), steps that a wave may run past a step's row in the rings, and the
+    // synapses of slot 0 (near lists [lif_total][kNearCap], their lengths, the
+    // largest length past kNearRegs)
+    int H, slot_off, run_max;
+    uint2* near;
+    int* ncnt;
+    int* nmax;
+    int* act;                          // [B][T] steps with spikes, last first
+    int* nact;                         // [B]
     ClusterArgs cl;                    // cluster mode (cl.G > 0): adjoint rings in LDS, row width 64
     int cl_off;                        // cluster mode: LDS byte offset of the exchange staging (shares
                                        // [NL NP][kClKC][4] fp64, slot totals [NL kClKC] fp64, own
@@ -301,6 +327,10 @@ hipError_t launch_copy_state(const float* src, int stride, int off, int n, int B
 hipError_t launch_readout_adjoint(const ReadoutBwdArgs& a, int threads, size_t lds, hipStream_t s);
 hipError_t launch_backward_core(const CoreBwdArgs& a, int n_lif, int threads, size_t lds,
                                 hipStream_t s);
+hipError_t launch_backward_prep(const CoreBwdArgs& a, int n_lif, hipStream_t s);
+hipError_t launch_backward_split(const CoreBwdArgs& a, int n_lif, int np, size_t lds, hipStream_t s);
+bool backward_split_serves(int n_lif, int np, int maxn);
+hipError_t set_split_lds_limits(size_t bytes, int* bad);
 hipError_t launch_group(const GroupArgs& a, int B, hipStream_t s);
 hipError_t launch_gradients(const GradArgs& a, int J, int KL, int threads, size_t lds, hipStream_t s);
 hipError_t launch_grad_reduce(const GradArgs& a, int P, hipStream_t s);
