@@ -71,10 +71,18 @@ struct snn_net {
     int bpart_off;              // backward-core LDS plan: partial jump sums or jump slots
     int split_H;                // helper waves of the split backward core (0: not used)
     int split_run;              // steps that its waves may run past a step's ring row
-    uint2* near;                // its synapses of slot 0 (see CoreBwdArgs)
+    int split_f, split_NS, split_waves;   // the split forward core serves the network; its scatter
+                                // waves, and the most waves it may have
+    int split_np;               // most LIF-sourced projections into or out of a LIF layer
+    uint2* near;                // tables of the split cores (split_tables_kernel)
     int* ncnt;
-    int* act;
-    uint2* far;                 // its far table, every projection
+    uint2* far;
+    uint2* ffar;
+    uint2* ro_far;              // the fused readout's table
+    uint2* post;
+    int* pcnt;
+    long long foff[SNN_MAXP], poff[SNN_MAXP];   // a projection's offsets in far, pcnt (post: times kPostCap)
+    int* act;                   // backward: steps with spikes
     JumpData* jump;             // [n_lif][B][cap]
     int bring_mode[SNN_MAX_LAYERS];   // adjoint ring of a LIF layer: -2 none, -1 HBM, >= 0 LDS
                                       // byte offset
@@ -174,7 +182,8 @@ static void free_all(snn_net* n) {
                     n->A2,       n->in_goff,   n->in_gstep, n->st,
                     n->gpart,   n->ws,      n->steptab, n->mom,   n->xlp_out, n->ncount,
                     n->nterm,   n->clx,     n->masks, n->near, n->ncnt, n->act,
-                    n->far,     n->jump};
+                    n->far,     n->jump,  n->post,  n->pcnt, n->ffar,
+                    n->ro_far};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     for (int p = 0; p < SNN_MAXP; ++p)
@@ -354,6 +363,10 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
             e = set_backward_lds_limits(kLds, &bad);
         }
         if (e == hipSuccess) {
+            what = "split forward core LDS limits";
+            e = set_forward_split_lds_limits(kLds, &bad);
+        }
+        if (e == hipSuccess) {
             what = "split backward core LDS limits";
             e = set_split_lds_limits(kLds, &bad);
         }
@@ -405,10 +418,31 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
             used = 0;
             for (int p = 0; p < t.P; ++p) t.fring[p] = -1;
         }
+        // the split core: neuron waves, a scatter wave per 64 columns of every
+        // ring, a record wave (and the readout's), its head of the LDS before
+        // the rings
+        {
+            int ns = 0, into[SNN_MAX_LAYERS] = {0};
+            net->split_np = net->cl_np;
+            for (int p = 0; p < t.P; ++p) {
+                if (t.pre[p] == 0 || t.kind[t.post[p]] != SNN_LIF) continue;
+                ns += (t.n[t.post[p]] + 63) / 64;
+                net->split_np = std::max(net->split_np, ++into[t.post[p]]);
+            }
+            const int head = net->cl_np > 0 ? forward_split_head(t.n_lif, net->split_np, nwaves, &net->split_waves) : -1;
+            if (rings_lds && !(want_cl && coop && force_cl) && head >= 0 && nwaves + ns + 1 <= net->split_waves &&
+                align16(head) + used <= kLds) {
+                net->split_f = 1;
+                net->split_NS = ns;
+                for (int p = 0; p < t.P; ++p)
+                    if (t.fring[p] >= 0) t.fring[p] += (int)(align16(head) / sizeof(float));
+                used += align16(head);
+            }
+        }
         net->mask_off = (int)align16(used);
         net->ids_off = net->mask_off +
                        (int)align16((size_t)3 * std::max(t.n_lif, 1) * nwaves * sizeof(unsigned long long));
-        net->lds_core_f = net->mask_off + masks;
+        net->lds_core_f = net->split_f ? align16(used) : net->mask_off + masks;
         // cluster mode where the rings do not fit (or on request): each
         // workgroup holds 64 columns of every ring, the masks of all G
         // workgroups [3][NL][G] and an abort flag
@@ -442,7 +476,8 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         // arrival ring [S_out + 1][C] after the masks
         const int feed_l = t.pre[t.out_p];
         const size_t ro_ring = (size_t)(t.Sp[t.out_p] + 1) * C * sizeof(float);
-        if (!t.out_lif && feed_l != 0 && net->core_threads <= 256 && C <= 64 && !net->cl_f &&
+        const bool ro_room = net->split_f ? nwaves + net->split_NS + 2 <= net->split_waves : net->core_threads <= 256;
+        if (!t.out_lif && feed_l != 0 && ro_room && C <= 64 && !net->cl_f &&
             !(opts->flags & SNN_FLAG_SEPARATE_READOUT) &&
             align16(net->lds_core_f) + ro_ring <= kLds) {
             net->ro_fused = 1;
@@ -669,11 +704,25 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
     ALLOC(net->rec_I, nl * B * cap);
     ALLOC(net->rec_idx, nl * B * T1);
     ALLOC(net->rec_cnt, nl * B);
-    if (net->split_H > 0) {
+    if (net->split_f || net->split_H > 0) {
+        long long f = 0, q = 0;
+        for (int p = 0; p < t.P; ++p) {
+            if (t.pre[p] == 0 || t.kind[t.post[p]] != SNN_LIF) continue;
+            net->foff[p] = f;
+            net->poff[p] = q;
+            f += (long long)(t.n[t.pre[p]] + 1) * t.n[t.post[p]];
+            q += t.n[t.post[p]];
+        }
+        ALLOC(net->far, (size_t)f);
+        ALLOC(net->ffar, (size_t)f);
+        if (net->split_f && net->ro_fused) ALLOC(net->ro_far, (size_t)(t.n[feed] + 1) * C);
+        ALLOC(net->post, (size_t)q * kPostCap);
+        ALLOC(net->pcnt, (size_t)q);
         ALLOC(net->near, (size_t)t.lif_total * kNearCap);
-        ALLOC(net->ncnt, (size_t)t.lif_total + 1);
+        ALLOC(net->ncnt, (size_t)t.lif_total);
+    }
+    if (net->split_H > 0) {
         ALLOC(net->act, B * T + B);
-        ALLOC(net->far, (size_t)net->n_params);
         ALLOC(net->jump, nl * B * cap);
     }
     ALLOC(net->masks, nl * B * T * (size_t)nwaves);
@@ -852,6 +901,32 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
     HIP_TRY(net, launch_round_delays(D, W, t.woff, net->cnt, t.P, t.dmax, net->slot, net->ws,
                                      net->st, s));
 
+    if (net->split_f || net->split_H > 0) {
+        SplitTables st{};
+        st.lif_total = t.lif_total;
+        st.rowblocks = (t.lif_total + 7) / 8;
+        for (int p = 0; p < t.P; ++p) {
+            const int pre = t.pre[p], q = t.post[p];
+            if (pre == 0 || t.kind[q] != SNN_LIF) continue;
+            const int li = t.lif[pre];
+            st.out[li][st.npost[li]++] = st.np;
+            st.pr[st.np++] = SplitProj{t.n[pre], t.n[q], t.Sp[p], net->ws + t.woff[p], net->far + net->foff[p],
+                                       net->ffar + net->foff[p],
+                                       net->post + net->poff[p] * kPostCap, net->pcnt + net->poff[p]};
+        }
+        for (int l = 1; l < t.L; ++l)
+            if (t.kind[l] == SNN_LIF) st.n[t.lif[l]] = t.n[l];
+        if (net->split_f && net->ro_fused) {
+            st.ro = SplitProj{t.n[t.pre[t.out_p]], t.n[t.out_l], t.Sp[t.out_p], net->ws + t.woff[t.out_p], nullptr,
+                              net->ro_far, nullptr, nullptr};
+            st.ro_l = t.lif[t.pre[t.out_p]];
+        }
+        st.near = net->near;
+        st.ncnt = net->ncnt;
+        st.st = net->st;
+        HIP_TRY(net, launch_split_tables(st, s));
+    }
+
     InScanArgs sa{};
     sa.B = t.B;
     sa.T = t.T;
@@ -896,7 +971,11 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
                 y.in_S[y.nin] = t.Sp[p];
                 y.in_ring_lds[y.nin] = t.fring[p];
                 y.in_ring[y.nin] = net->fring[p];
+                if (pre != 0) ++y.nrec;
                 if (pre != 0) {
+                    y.in_ws[y.nin] = net->ws + t.woff[p];
+                    y.in_post[y.nin] = net->post + net->poff[p] * kPostCap;
+                    y.in_pcnt[y.nin] = net->pcnt + net->poff[p];
                     // position of p among the LIF-post projections of its source layer
                     int k = 0;
                     for (int p2 = 0; p2 < p; ++p2)
@@ -915,6 +994,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
                 y.ring_lds[y.npost] = t.fring[p];
                 y.ring[y.npost] = net->fring[p];
                 y.ws[y.npost] = net->ws + t.woff[p];
+                y.ffar[y.npost] = net->ffar + net->foff[p];
                 ++y.npost;
             }
             for (int k = y.npost; k < 2; ++k) {
@@ -935,7 +1015,9 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             y.rec_I = net->rec_I + li * B * cap;
             y.rec_idx = net->rec_idx + li * B * (size_t)(t.T + 1);
             y.rec_cnt = net->rec_cnt + li * B;
-            y.steptab = net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
+            // (the split backward core does not read the step table)
+            y.steptab = net->split_f && net->split_H > 0 ? nullptr
+                                                         : net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
             y.masks = net->masks + li * B * (size_t)t.T * (net->core_threads / 64);
             y.ncount = net->reg_on ? net->ncount + t.lif_off[l] : nullptr;
             y.out_count = records[li].count;
@@ -957,10 +1039,15 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             a.ro_loss = t.loss;
             a.ro_scale = t.rscale;
             a.ro_ws = net->ws + t.woff[t.out_p];
+            a.ro_far = net->ro_far;
             a.z = net->z;
             a.nstar = net->nstar;
         }
-        if (net->cl_f)
+        a.NS = net->split_NS;
+        a.ro_end = (int)net->lds_core_f;
+        if (net->split_f)
+            TIMED(net, K_CORE, launch_forward_split(a, t.n_lif, net->split_np, net->lds_core_f, s));
+        else if (net->cl_f)
             TIMED(net, K_CORE, launch_forward_clusters(net, a, s));
         else
             TIMED(net, K_CORE, launch_forward_core(a, t.n_lif, net->core_threads + (net->ro_fused ? 64 : 0),
@@ -1218,7 +1305,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
                 const int q = t.post[p];
                 if (t.pre[p] != l || t.kind[q] != SNN_LIF) continue;
                 y.ws[y.npost] = net->ws + t.woff[p];
-                y.far[y.npost] = net->far + t.woff[p];
+                y.far[y.npost] = net->far + net->foff[p];
                 y.nq[y.npost] = t.n[q];
                 y.npre[y.npost] = t.n[l];
                 y.qS[y.npost] = t.Sb[q];
@@ -1232,7 +1319,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
                     const int q = t.post[p];
                     if (t.pre[p] == 0 || t.kind[q] != SNN_LIF) continue;
                     y.ws[k] = net->ws + t.woff[p];
-                    y.far[k] = net->far + t.woff[p];
+                    y.far[k] = net->far + net->foff[p];
                     y.nq[k] = t.n[q];
                     y.npre[k] = t.n[t.pre[p]];
                     y.qS[k] = t.Sb[q];
@@ -1256,11 +1343,9 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
         a.run_max = net->split_run;
         a.near = net->near;
         a.ncnt = net->ncnt;
-        a.nmax = net->ncnt + t.lif_total;
         a.act = net->act;
         a.nact = net->act + (size_t)t.B * t.T;
         if (net->split_H > 0) {
-            HIP_TRY(net, launch_zero_ints(a.nmax, 1, s));
             HIP_TRY(net, launch_backward_prep(a, t.n_lif, s));
             TIMED(net, K_BCORE, launch_backward_split(a, t.n_lif, net->cl_np, net->lds_core_b, s));
         } else if (net->cl_b)

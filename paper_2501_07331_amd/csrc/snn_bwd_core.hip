@@ -23,7 +23,7 @@
 // a step earlier, so the helpers take them while the neuron waves run the
 // step's dynamics.  The few terms with slot 0 are left to the spiking neuron's
 // own lane, which holds the first of them (post neuron, weight) in registers
-// (backward_prep_kernel) and reads the step's own row after the step's barrier.
+// (split_tables_kernel) and reads the step's own row after the step's barrier.
 // Where some neuron has more than kNearCap synapses of slot 0 (delays near
 // zero throughout), the helpers take those terms too, between the step's
 // barrier and a second one.
@@ -57,78 +57,42 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
     return x;
 }
 
-// What the core needs of a call beside the records.
-//  workgroups [0, B): the steps of sample b that have spikes of any LIF layer,
-//      last first (act), and their number; for every record its jump's data
-//      (jump: A2, k, r; the jump is lambda_V <- k lambda_V + r A with r = 1 /
-//      (I- - theta), k = 1 + theta r, that is lambda_V + (theta lambda_V + A) /
-//      (I- - theta); r < 0 marks a skipped one, I- <= theta).
-//  workgroups from B on, one wave per neuron of the LIF layers: its rows of
-//      the far table (far: weight bits, 0 for slot 0; slot times the bytes of
-//      a ring row), which leaves a delayed sum three address operations a
-//      term and no mask; and its synapses of slot 0, projections then posts in
-//      order: the first kNearCap (weight bits; LDS byte offset of the post's
-//      ring column, projection << 16), their number, and the largest number
-//      past kNearRegs over all neurons (nmax, zero before the launch).
+// What the core needs of a call beside the records, per sample: the steps that
+// have spikes of any LIF layer, last first (act), and their number; for every
+// record its jump's data: A2, k, r; the jump is lambda_V <- k lambda_V + r A
+// with r = 1 / (I- - theta), k = 1 + theta r, that is lambda_V + (theta
+// lambda_V + A) / (I- - theta); r < 0 marks a skipped one, I- <= theta.
 __global__ void __launch_bounds__(256) backward_prep_kernel(CoreBwdArgs a, int nl) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if ((int)blockIdx.x < a.B) {
-        const int b = blockIdx.x;
-        for (int l = 0; l < nl; ++l) {
-            const BwdLayer& y = a.ly[l];
-            const size_t r0 = (size_t)b * a.cap;
-            const int cnt = y.rec_idx[(size_t)b * (a.T + 1) + a.T];
-            for (int q = tid; q < cnt; q += 256) {
-                // tau_m dV/dt just before the crossing is I- - theta (V- = theta)
-                const double den = __dsub_rn((double)y.recI[r0 + q], a.theta), r = 1.0 / den;
-                JumpData* o = y.jump + r0 + q;
-                o->A = y.A2 ? y.A2[r0 + q] : 0.0;
-                o->k = __fma_rn(a.theta, r, 1.0);
-                o->r = den > 0.0 ? r : -1.0;
-            }
+    const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x;
+    for (int l = 0; l < nl; ++l) {
+        const BwdLayer& y = a.ly[l];
+        const size_t r0 = (size_t)b * a.cap;
+        const int cnt = y.rec_idx[(size_t)b * (a.T + 1) + a.T];
+        for (int q = tid; q < cnt; q += 256) {
+            // tau_m dV/dt just before the crossing is I- - theta (V- = theta)
+            const double den = __dsub_rn((double)y.recI[r0 + q], a.theta), r = 1.0 / den;
+            JumpData* o = y.jump + r0 + q;
+            o->A = y.A2 ? y.A2[r0 + q] : 0.0;
+            o->k = __fma_rn(a.theta, r, 1.0);
+            o->r = den > 0.0 ? r : -1.0;
         }
-        if (wave != 0) return;
-        int* act = a.act + (size_t)b * a.T;
-        int cnt = 0;
-        for (int n0 = a.T - 1; n0 >= 0; n0 -= 64) {
-            const int n = n0 - lane;
-            bool any = false;
-            for (int l = 0; l < nl; ++l) {
-                const int* idx = a.ly[l].rec_idx + (size_t)b * (a.T + 1) + max(n, 0);
-                any |= idx[1] > idx[0];
-            }
-            any = any && n >= 0;
-            const unsigned long long m = __ballot(any);
-            if (any) act[cnt + lanes_below(m)] = n;
-            cnt += __popcll(m);
-        }
-        if (lane == 0) a.nact[b] = cnt;
-        return;
     }
-    int i = ((int)blockIdx.x - a.B) * 4 + wave, l = 0;
-    if (i >= a.lif_total) return;
-    while (i >= a.ly[l].n) i -= a.ly[l++].n;
-    const BwdLayer& y = a.ly[l];
-    uint2* near = a.near + (size_t)(y.lif_off + i) * kNearCap;
+    if (tid >= 64) return;
+    int* act = a.act + (size_t)b * a.T;
     int cnt = 0;
-    for (int pp = 0; pp < y.npost; ++pp) {
-        const int nq = y.nq[pp];
-        for (int j0 = 0; j0 < nq; j0 += 64) {
-            const int j = j0 + lane;
-            const size_t k = (size_t)i * nq + min(j, nq - 1);
-            const uint2 e = y.ws[pp][k];
-            const bool zero = j < nq && e.y == 0;
-            const unsigned long long m = __ballot(zero);
-            const int pos = cnt + lanes_below(m);
-            if (j < nq) y.far[pp][k] = make_uint2(zero ? 0u : e.x, e.y * (unsigned)(nq * 8));
-            if (zero && pos < kNearCap) near[pos] = make_uint2(e.x, (unsigned)(j * 8) | ((unsigned)pp << 16));
-            cnt += __popcll(m);
+    for (int n0 = a.T - 1; n0 >= 0; n0 -= 64) {
+        const int n = n0 - lane;
+        bool any = false;
+        for (int l = 0; l < nl; ++l) {
+            const int* idx = a.ly[l].rec_idx + (size_t)b * (a.T + 1) + max(n, 0);
+            any |= idx[1] > idx[0];
         }
+        any = any && n >= 0;
+        const unsigned long long m = __ballot(any);
+        if (any) act[cnt + lanes_below(m)] = n;
+        cnt += __popcll(m);
     }
-    if (lane == 0) {
-        a.ncnt[y.lif_off + i] = cnt;
-        if (cnt > kNearRegs) atomicMax(a.nmax, cnt);
-    }
+    if (lane == 0) a.nact[b] = cnt;
 }
 
 // MC: 64-post chunks of the widest LIF-post layer, at most.
@@ -216,7 +180,8 @@ struct BwdSplit {
 
     // This lane's terms of slots >= 1 of one spike of layer l, subtracted from
     // v: the far table's weights times the ring cells of the arrivals (rows of
-    // steps past T - 1 were never written: zero).  nm: byte offset of the
+    // steps past T - 1 were never written: zero; the table's entries of slot 0
+    // have weight 0).  nm: byte offset of the
     // step's own row in each post ring.
     static __device__ __forceinline__ void far_terms(const CoreBwdArgs& a, const int (&nm)[NL][NP], int l, int lane,
                                                      const Row& R, double& v) {
@@ -236,7 +201,7 @@ struct BwdSplit {
 #pragma unroll
                     for (int u = 0; u < CH; ++u) {
                         const unsigned x = (unsigned)(nm[m][pp] + min((c0 + u) * 64 + lane, nq - 1) * 8) +
-                                           R.w[pp][c0 + u].y;
+                                           R.w[pp][c0 + u].y * 8u;
                         d[u] = *(const lds_f64*)(ring + min(x, x - bytes));     // x < 2 rings
                     }
 #pragma unroll
@@ -592,7 +557,7 @@ struct BwdSplit {
     static __device__ void run(const CoreBwdArgs& a) {
         const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const bool lists = *a.nmax <= kNearCap;
+        const bool lists = a.st->near_pre <= kNearCap;
         // the rings start at zero: rows not written yet are read, and masked
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
@@ -635,7 +600,7 @@ const void* split_kernel(int n_lif, int np, int mc) {
 }  // namespace
 
 hipError_t launch_backward_prep(const CoreBwdArgs& a, int n_lif, hipStream_t s) {
-    hipLaunchKernelGGL(backward_prep_kernel, dim3(a.B + (a.lif_total + 3) / 4), dim3(256), 0, s, a, n_lif);
+    hipLaunchKernelGGL(backward_prep_kernel, dim3(a.B), dim3(256), 0, s, a, n_lif);
     return hipGetLastError();
 }
 

@@ -14,6 +14,8 @@ __global__ void reset_status_kernel(DevStatus* st) {
         st->degenerate = 0;
         st->reg_loss = 0.0;
         st->cl_abort = 0;
+        st->near_pre = 0;
+        st->near_post = 0;
         for (int l = 0; l < SNN_MAX_LAYERS; ++l) st->layer_spikes[l] = 0;
     }
 }

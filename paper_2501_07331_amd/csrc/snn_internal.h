@@ -23,6 +23,8 @@ struct DevStatus {
     unsigned long long degenerate;   // skipped jumps (I- <= theta)
     unsigned long long layer_spikes[SNN_MAX_LAYERS];   // per LIF layer, all samples
     double reg_loss;                 // spike-count penalty of the last forward
+    int near_pre, near_post;         // most near synapses from / to a neuron of a LIF -> LIF
+                                     // projection (counted past kNearRegs / past 4)
     int cl_abort;                    // a cluster exchange gave up waiting (the results are void)
 };
 
@@ -102,6 +104,10 @@ struct FwdLayer {
     int in_S[2];                       //   LIF sources: that projection's ring slots,
     int in_ring_lds[2];                //   its ring (LDS float offset, or the HBM ring
     float* in_ring[2];                 //   [B][S+1][n])
+    int nrec;                          // how many are LIF-sourced (layer 0's first is the inputs')
+    const uint2* in_ws[2];             // split core, LIF sources: (weight bits, slot) [n_pre][n],
+    const uint2* in_post[2];           //   the posts' near synapses [n][kPostCap]
+    const int* in_pcnt[2];             //   and their number [n] (split_tables_kernel)
     int npost;                         // LIF-post projections out of the layer (recurrent, then
                                        // feed-forward); entries past npost repeat a valid one
     int nq[2];                         //   post neurons
@@ -110,12 +116,13 @@ struct FwdLayer {
     int ring_lds[2];                   //   delay ring [S+1][nq] (row S: dummy): LDS float offset,
     float* ring[2];                    //   or the HBM ring [B][S+1][nq]
     const uint2* ws[2];                //   (weight bits, slot) [n][nq]
+    const uint2* ffar[2];              //   split core: far table [n+1][nq] (split_tables_kernel)
     int* rec_n;                        // [B][cap] records: neuron, step, I-
     int* rec_s;
     float* rec_I;
     int* rec_idx;                      // [B][T+1] first record of each step
     int* rec_cnt;                      // [B]
-    int* steptab;                      // [B][T][SNN_STEP_ROW]
+    int* steptab;                      // [B][T][SNN_STEP_ROW], or NULL (split core only)
     unsigned long long* masks;         // [B][T][NW] spikes of each 64 neurons, one bit each
     int* ncount;                       // [n] spikes per neuron over the batch (added), or NULL
     int* out_count;                    // caller's records: [B], [B][cap], [B][cap]
@@ -140,9 +147,38 @@ struct CoreFwdArgs {
     int ro_C, ro_feed, ro_nfeed, ro_S, ro_off, ro_loss;
     float ro_scale;
     const uint2* ro_ws;                // readout projection (weight bits, slot) [ro_nfeed][ro_C]
+    const uint2* ro_far;               // split core: its table [ro_nfeed + 1][ro_C] (split_tables_kernel)
     float* z;                          // [B][C]
     int* nstar;                        // [B][C]
+    int NS, ro_end;                    // split core: scatter waves, end of its LDS (bytes)
     ClusterArgs cl;                    // cluster mode (cl.G > 0): every ring in LDS, row width 64
+};
+
+// Synapses that the split cores keep out of the rings: of slot 0 from a neuron
+// (backward core: at most kNearCap, kNearRegs of them in the registers of its
+// lane) and of slots 0 and 1 to a neuron (forward core: at most kPostCap).
+// Delays drawn from 0 .. 50 give a neuron 2.6 of the former and 7.7 of the
+// latter among 256.
+constexpr int kNearRegs = 8, kNearCap = 24, kPostCap = 32;
+
+// One LIF -> LIF projection and its tables (split_tables_kernel).
+struct SplitProj {
+    int npre, nq, S;
+    const uint2* ws;                   // (weight bits, slot) [npre][nq]
+    uint2* far;                        // [npre][nq] backward core
+    uint2* ffar;                       // [npre + 1][nq] forward core
+    uint2* post;                       // [nq][kPostCap]
+    int* pcnt;                         // [nq]
+};
+struct SplitTables {
+    int rowblocks, lif_total, np;
+    int n[SNN_MAX_LIF], npost[SNN_MAX_LIF], out[SNN_MAX_LIF][2];   // LIF layers, their projections in pr
+    SplitProj pr[SNN_MAXP];
+    SplitProj ro;                      // the fused readout's projection (ro.ffar NULL: none), from layer ro_l
+    int ro_l;
+    uint2* near;                       // [lif_total][kNearCap]
+    int* ncnt;                         // [lif_total]
+    DevStatus* st;
 };
 
 struct ReadoutArgs {
@@ -181,11 +217,6 @@ struct ReadoutBwdArgs {
     int tab_lds;                       // 1: the [T][C] table of lambda_I - lambda_V lives in LDS
 };
 
-// Synapses of slot 0 that a spiking neuron's own lane of the split backward
-// core adds: up to kNearCap per neuron, the first kNearRegs from registers.
-// (Delays drawn from 0 .. 50 give a neuron 2.6 of them among 256 posts.)
-constexpr int kNearRegs = 8, kNearCap = 24;
-
 // A recorded spike's jump lambda_V <- k lambda_V + r A (A: the numerator's sum
 // so far; r < 0: skipped).
 struct JumpData {
@@ -209,7 +240,7 @@ struct BwdLayer {
     int qring_lds[2];                  //   its adjoint ring (LDS byte offset, or -1: global qring)
     double* qring[2];
     const uint2* ws[2];                //   (weight bits, slot) [n][nq]
-    uint2* far[2];                     //   split core: its far table [n][nq]
+    const uint2* far[2];               //   split core: far table [n][nq] (split_tables_kernel)
     JumpData* jump;                    // split core: [B][cap]
     const float* recI;                 // [B][cap] I- of the records
     const int* recn;                   // [B][cap] neuron of the records
@@ -228,13 +259,11 @@ struct CoreBwdArgs {
     DevStatus* st;
     int part_off;                      // LDS byte offset of the partial jump sums
     // split core: helper waves, LDS byte offset of the jump slots
-    // ([2][lif_total] JumpData), steps that a wave may run past a step's row in the rings, and the
-    // synapses of slot 0 (near lists [lif_total][kNearCap], their lengths, the
-    // largest length past kNearRegs)
+    // ([2][lif_total] JumpData), steps that a wave may run past a step's row in
+    // the rings, the synapses of slot 0 (split_tables_kernel)
     int H, slot_off, run_max;
-    uint2* near;
-    int* ncnt;
-    int* nmax;
+    const uint2* near;
+    const int* ncnt;
     int* act;                          // [B][T] steps with spikes, last first
     int* nact;                         // [B]
     ClusterArgs cl;                    // cluster mode (cl.G > 0): adjoint rings in LDS, row width 64
@@ -327,6 +356,10 @@ hipError_t launch_copy_state(const float* src, int stride, int off, int n, int B
 hipError_t launch_readout_adjoint(const ReadoutBwdArgs& a, int threads, size_t lds, hipStream_t s);
 hipError_t launch_backward_core(const CoreBwdArgs& a, int n_lif, int threads, size_t lds,
                                 hipStream_t s);
+int forward_split_head(int n_lif, int np, int nw, int* waves);
+hipError_t launch_split_tables(const SplitTables& a, hipStream_t s);
+hipError_t launch_forward_split(const CoreFwdArgs& a, int n_lif, int np, size_t lds, hipStream_t s);
+hipError_t set_forward_split_lds_limits(size_t bytes, int* bad);
 hipError_t launch_backward_prep(const CoreBwdArgs& a, int n_lif, hipStream_t s);
 hipError_t launch_backward_split(const CoreBwdArgs& a, int n_lif, int np, size_t lds, hipStream_t s);
 bool backward_split_serves(int n_lif, int np, int maxn);
