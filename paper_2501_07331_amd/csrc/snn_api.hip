@@ -67,10 +67,11 @@ struct snn_net {
     int ro_fused, ro_off;       // the LI readout runs as one more wave of the forward core
     int read_threads;           // readout workgroup size
     size_t lds_core_f, lds_core_b, lds_scan, lds_read, lds_grad, lds_radj;
-    int mask_off, ids_off, scan_tb, table_lds;
+    int mask_off, ids_off, scan_tb, scan_segs, table_lds;
     int bpart_off;              // backward-core LDS plan: partial jump sums or jump slots
     int split_H;                // helper waves of the split backward core (0: not used)
     int split_run;              // steps that its waves may run past a step's ring row
+    int ff;                     // one LIF layer that feeds no LIF layer: snn_ff_core.hip
     int split_f, split_NS, split_waves;   // the split forward core serves the network; its scatter
                                 // waves, and the most waves it may have
     int split_np;               // most LIF-sourced projections into or out of a LIF layer
@@ -154,6 +155,24 @@ struct snn_net {
     snn_stats stats;
     char err[256];
 };
+
+// Segments of a trial in the input scan: the segments of all samples run in
+// rounds of as many waves as the CUs' LDS holds rings; a round takes a pass over
+// its segment's steps and the S - 1 before them, and zeroing the ring (a step's
+// worth per eight rows).  Fewest segments within 5 % of the best.
+static int scan_segments(int T, int S, int waves, size_t lds, int n_cu) {
+    const long long slots = (long long)n_cu * std::max<long long>(1, std::min<long long>(8, kLds / lds));
+    auto cost = [&](int k) {
+        const long long L = (T + k - 1) / k;
+        return ((long long)waves * k + slots - 1) / slots * (L + (k > 1 ? S - 1 : 0) + S / 8);
+    };
+    const int most = std::max(1, std::min(32, T / 16));
+    long long best = cost(1);
+    for (int k = 2; k <= most; ++k) best = std::min(best, cost(k));
+    int k = 1;
+    while (k < most && cost(k) * 100 > best * 105) ++k;
+    return k;
+}
 
 static int fail(snn_net* net, int code, const char* fmt, ...) {
     if (net) {
@@ -477,7 +496,10 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         const int feed_l = t.pre[t.out_p];
         const size_t ro_ring = (size_t)(t.Sp[t.out_p] + 1) * C * sizeof(float);
         const bool ro_room = net->split_f ? nwaves + net->split_NS + 2 <= net->split_waves : net->core_threads <= 256;
-        if (!t.out_lif && feed_l != 0 && ro_room && C <= 64 && !net->cl_f &&
+        // (a layer that feeds no LIF layer has a core of its own, without a
+        // readout wave)
+        net->ff = t.n_lif == 1 && net->cl_np == 0;
+        if (!net->ff && !t.out_lif && feed_l != 0 && ro_room && C <= 64 && !net->cl_f &&
             !(opts->flags & SNN_FLAG_SEPARATE_READOUT) &&
             align16(net->lds_core_f) + ro_ring <= kLds) {
             net->ro_fused = 1;
@@ -562,6 +584,7 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
     // at least 8
     net->scan_tb = std::max(8, std::min(64, 160 - t.Sp[0]));
     net->lds_scan = (size_t)(t.Sp[0] + net->scan_tb) * 64 * sizeof(float);
+    net->scan_segs = scan_segments(t.T, t.Sp[0], t.B * ((t.n[1] + 63) / 64), net->lds_scan, n_cu);
     // readout forward: arrival table [T + 1][C] (row T: dummy) in LDS when it fits
     // readout: groups of ceil(C / 64) waves, each building a window of the
     // arrival table; up to 1024 threads
@@ -934,6 +957,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
     sa.n_in = t.n_in;
     sa.n1 = t.n[1];
     sa.TB = net->scan_tb;
+    sa.segs = net->scan_segs;
     sa.ws0 = net->ws;
     sa.in_neuron = in->neuron;
     sa.in_step = in->step;
@@ -1015,9 +1039,9 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             y.rec_I = net->rec_I + li * B * cap;
             y.rec_idx = net->rec_idx + li * B * (size_t)(t.T + 1);
             y.rec_cnt = net->rec_cnt + li * B;
-            // (the split backward core does not read the step table)
-            y.steptab = net->split_f && net->split_H > 0 ? nullptr
-                                                         : net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
+            // (the split and feed-forward backward cores do not read the step table)
+            y.steptab = net->ff || (net->split_f && net->split_H > 0)
+                            ? nullptr : net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
             y.masks = net->masks + li * B * (size_t)t.T * (net->core_threads / 64);
             y.ncount = net->reg_on ? net->ncount + t.lif_off[l] : nullptr;
             y.out_count = records[li].count;
@@ -1045,7 +1069,9 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
         }
         a.NS = net->split_NS;
         a.ro_end = (int)net->lds_core_f;
-        if (net->split_f)
+        if (net->ff)
+            TIMED(net, K_CORE, launch_forward_ff(a, s));
+        else if (net->split_f)
             TIMED(net, K_CORE, launch_forward_split(a, t.n_lif, net->split_np, net->lds_core_f, s));
         else if (net->cl_f)
             TIMED(net, K_CORE, launch_forward_clusters(net, a, s));
@@ -1226,6 +1252,9 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
     // latency-bound adjoint core (forked after the readout adjoint, whose
     // workgroups take a whole CU's LDS); the gradients wait for them
     const hipStream_t g_s = net->aux;
+    // the split backward core's 16 waves leave a CU room (registers) for four
+    // more: with 512 threads the grouping waited for the core's workgroups to end
+    const int group_threads = net->split_H > 0 ? 256 : 512;
     HIP_TRY(net, hipEventRecord(net->fork, s));
     HIP_TRY(net, hipStreamWaitEvent(g_s, net->fork, 0));
     net->ran[K_GROUP] = 1;
@@ -1241,7 +1270,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
         g.g_step = in_gstep;
         g.stage_cap = (int)std::min<long long>(net->in_nnz, kGroupStage);
         g.st = net->st;
-        HIP_TRY(net, launch_group(g, t.B, g_s));
+        HIP_TRY(net, launch_group(g, t.B, group_threads, g_s));
     }
     for (int l = 1; l < t.L; ++l) {
         if (t.kind[l] != SNN_LIF) continue;
@@ -1256,7 +1285,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
         g.g_step = net->rec_gstep + li * gstep_stride(t.B, t.cap);
         g.stage_cap = std::min(t.cap, kGroupStage);
         g.st = net->st;
-        HIP_TRY(net, launch_group(g, t.B, g_s));
+        HIP_TRY(net, launch_group(g, t.B, group_threads, g_s));
     }
     if (net->timing) HIP_TRY(net, hipEventRecord(net->ev[2 * K_GROUP + 1], g_s));
     HIP_TRY(net, hipEventRecord(net->join, g_s));
@@ -1345,7 +1374,9 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
         a.ncnt = net->ncnt;
         a.act = net->act;
         a.nact = net->act + (size_t)t.B * t.T;
-        if (net->split_H > 0) {
+        if (net->ff) {
+            TIMED(net, K_BCORE, launch_backward_ff(a, s));
+        } else if (net->split_H > 0) {
             HIP_TRY(net, launch_backward_prep(a, t.n_lif, s));
             TIMED(net, K_BCORE, launch_backward_split(a, t.n_lif, net->cl_np, net->lds_core_b, s));
         } else if (net->cl_b)

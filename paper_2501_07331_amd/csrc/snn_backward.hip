@@ -486,7 +486,6 @@ struct BwdCore {
             double A2[NL];
 #pragma unroll
             for (int l = 0; l < NL; ++l) {
-                const BwdLayer& y = a.ly[l];
                 const int cnt = A.cnt3[l] - r * KP;          // spikes left from this round on
                 int ids[KP];
                 const int capm = max(a.cap - 1, 0);
@@ -1040,7 +1039,7 @@ __global__ void __launch_bounds__(64 * (1 + NL * NP)) backward_cluster_kernel(Co
 // device memory), each neuron's steps sorted (thread per neuron, insertion
 // sort: the spikes arrive in step order, so a neuron's list is nearly
 // sorted), then written out.
-__global__ void __launch_bounds__(1024) group_kernel(GroupArgs a) {
+__global__ void __launch_bounds__(512) group_kernel(GroupArgs a) {
     if (a.st->bad_input) return;
     const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wv = tid >> 6;
@@ -1370,10 +1369,23 @@ __global__ void grad_reduce_kernel(GradArgs a, int P) {
     if (g >= a.nparams) return;
     int p = 0;
     while (p + 1 < P && g >= a.woff[p + 1]) ++p;
+    // (in block order; the loads of eight blocks go out together: a network of
+    // few parameters has few threads here, and their memory latency is all there
+    // is to it)
     double su = 0.0, sd = 0.0;
-    for (int sb = 0; sb < a.SB; ++sb) {
-        su += a.part[((size_t)sb * 2 + 0) * a.nparams + g];
-        sd += a.part[((size_t)sb * 2 + 1) * a.nparams + g];
+    for (int s0 = 0; s0 < a.SB; s0 += 8) {
+        double x[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const size_t sb = (size_t)min(s0 + u, a.SB - 1);
+            x[u] = a.part[(sb * 2 + 0) * a.nparams + g];
+            y[u] = a.part[(sb * 2 + 1) * a.nparams + g];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            su = s0 + u < a.SB ? su + x[u] : su;
+            sd = s0 + u < a.SB ? sd + y[u] : sd;
+        }
     }
     const long long kk = g - a.woff[p];
     const double w = (double)__uint_as_float(a.ws[g].x);
@@ -1405,7 +1417,6 @@ template <int MAXT>
 static bool launch_core_t(const CoreBwdArgs& a, int n_lif, int np, bool rl, int threads, size_t lds,
                           hipStream_t s) {
     switch (n_lif * 4 + np) {
-        case 4 + 0: launch_core3<MAXT, 1, 0>(a, rl, threads, lds, s); return true;
         case 4 + 1: launch_core3<MAXT, 1, 1>(a, rl, threads, lds, s); return true;
         case 8 + 1: launch_core3<MAXT, 2, 1>(a, rl, threads, lds, s); return true;
         case 8 + 2: launch_core3<MAXT, 2, 2>(a, rl, threads, lds, s); return true;
@@ -1475,10 +1486,10 @@ hipError_t backward_cluster_occupancy(int n_lif, int np, int threads, size_t lds
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, threads, lds);
 }
 
-hipError_t launch_group(const GroupArgs& a, int B, hipStream_t s) {
-    if (a.stage_cap < 0) return hipErrorInvalidValue;
+hipError_t launch_group(const GroupArgs& a, int B, int threads, hipStream_t s) {
+    if (a.stage_cap < 0 || threads < 64 || threads > 512 || threads % 64) return hipErrorInvalidValue;
     const size_t lds = sizeof(int) * ((size_t)a.n + 1 + 16) + sizeof(unsigned short) * (size_t)a.stage_cap;
-    hipLaunchKernelGGL(group_kernel, dim3(B), dim3(1024), lds, s, a);
+    hipLaunchKernelGGL(group_kernel, dim3(B), dim3(threads), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1517,7 +1528,7 @@ hipError_t launch_grad_reduce(const GradArgs& a, int P, hipStream_t s) {
 }
 
 #define CORE_FNS2(M, R)                                                                          \
-    (const void*)backward_core_kernel<M, 1, bwd_prefetch(1), 0, R>, (const void*)backward_core_kernel<M, 1, bwd_prefetch(1), 1, R>, \
+    (const void*)backward_core_kernel<M, 1, bwd_prefetch(1), 1, R>, \
     (const void*)backward_core_kernel<M, 2, 4, 1, R>, (const void*)backward_core_kernel<M, 2, 4, 2, R>, \
     (const void*)backward_core_kernel<M, 3, 4, 1, R>, (const void*)backward_core_kernel<M, 3, 4, 2, R>, \
     (const void*)backward_core_kernel<M, 4, 4, 1, R>, (const void*)backward_core_kernel<M, 4, 4, 2, R>

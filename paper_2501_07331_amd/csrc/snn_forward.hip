@@ -106,9 +106,10 @@ __global__ void round_delays_kernel(RoundArgs a, uint8_t* slot, uint2* ws, DevSt
 
 // ------------------------------------------------------------------ input scan
 
-// Workgroup = (sample b, block of 64 posts of layer 1), one wave; lane j owns
-// post j.  The sample's input events stream by once, in emission order, in
-// chunks of KB = 8, and each chunk's weights are added into an LDS ring of
+// Workgroup = (sample b, block of 64 posts of layer 1, segment of steps), one
+// wave; lane j owns post j and the arrivals of steps [m0, m1) of the segment.
+// The events that can arrive there (emitted from S - 1 steps before the segment
+// on) stream by once, in emission order, in chunks of KB = 8, and each chunk's weights are added into an LDS ring of
 // R = S + TB - 1 arrival steps (row m % R; row R: dummy).  Rows of steps
 // before the first emission step of the next chunk are final (every later
 // event arrives at its emission step or after): they go out as A_in rows and
@@ -128,23 +129,54 @@ __global__ void round_delays_kernel(RoundArgs a, uint8_t* slot, uint2* ws, DevSt
 // wait at the next chunk start lets exactly the newest 8 operations (chunk
 // c + 1's weights) stay in flight.  The common path writes out at most two
 // rows per chunk and has no loop.
+//
+// The wave's serial pass over the events bounds the kernel, and its ring bounds
+// the waves of a CU, so where the samples alone leave CUs idle a trial is cut
+// into segments, at the price of S - 1 steps of events read twice per cut (the
+// host weighs the two: scan_segments).
+// Adds wv[q] to the cells at byte offset at[q] of the lane's column, in order, in
+// rounds of two (see column_add_rounds).
+__device__ __forceinline__ void ring_add(lds_f32* col, const int (&at)[KB], const float (&wv)[KB]) {
+    typedef __attribute__((address_space(3))) char lds_char;
+    auto cell = [&](int k) { return (lds_f32*)((lds_char*)col + at[k]); };
+#pragma unroll
+    for (int h = 0; h < KB; h += 2) {
+        const float v0 = *cell(h), v1 = *cell(h + 1);
+        const float s0 = __fadd_rn(v0, wv[h]);
+        const float s1 = __fadd_rn(at[h] == at[h + 1] ? s0 : v1, wv[h + 1]);
+        *cell(h) = s0;
+        *cell(h + 1) = s1;
+    }
+}
+
 __global__ void __launch_bounds__(64) input_scan_kernel(InScanArgs a) {
     if (a.st->bad_input) return;
     const int n1 = a.n1, T = a.T, TB = a.TB, R = a.S + a.TB - 1;
     const int nblk = (n1 + 63) >> 6;
-    const int b = blockIdx.x / nblk, jb = blockIdx.x - b * nblk;
+    const int seg = (int)blockIdx.x / (a.B * nblk), rest = (int)blockIdx.x - seg * a.B * nblk;
+    const int b = rest / nblk, jb = rest - b * nblk;
+    // the segment's bounds: the steps of the sample's events seg / segs and
+    // (seg + 1) / segs of the way through them (the events, not the steps, are
+    // its cost), the ends at 0 and T
+    const int Eb = a.in_idx[(size_t)b * (T + 1)], En = a.in_idx[(size_t)b * (T + 1) + T] - Eb;
+    const int k0 = Eb + (int)((long long)En * seg / a.segs), k1 = Eb + (int)((long long)En * (seg + 1) / a.segs);
+    const int m0 = seg == 0 ? 0 : En > 0 ? a.in_step[k0] : T;
+    const int m1 = seg + 1 == a.segs || En == 0 ? T : a.in_step[k1];
+    if (m0 >= m1) return;
+    const int first = max(0, m0 - (a.S - 1));
     const int lane = threadIdx.x, j = jb * 64 + lane;
     const bool live = j < n1;
     const int jc = min(j, n1 - 1);
     lds_f32* ring = (lds_f32*)smem + lane;                      // [R + 1][64]
     for (int r = 0; r <= R; ++r) ring[r * 64] = 0.0f;
     global_f32* out = (global_f32*)(a.A_in + (size_t)b * T * n1 + jc);
-    const int E0 = a.in_idx[(size_t)b * (T + 1)], E1 = a.in_idx[(size_t)b * (T + 1) + T];
-    int f = 0, fr = 0;                                           // rows < f written out; fr = f % R
+    const int E0 = a.in_idx[(size_t)b * (T + 1) + first], E1 = a.in_idx[(size_t)b * (T + 1) + m1];
+    int f = first, fr = 0;                                       // rows < f written out (before m0: dropped);
+                                                                 // fr: ring row of f
     auto flush_one = [&]() {
         const float v = ring[fr * 64];
         ring[fr * 64] = 0.0f;
-        if (live) out[(size_t)f * n1] = v;
+        if (live && f >= m0) out[(size_t)f * n1] = v;
         ++f;
         fr = (fr + 1 == R) ? 0 : fr + 1;
     };
@@ -184,6 +216,27 @@ __global__ void __launch_bounds__(64) input_scan_kernel(InScanArgs a) {
         auto add_chunk = [&](int e0, int stv, int u8, const uint2 (&w)[KB]) {
             const int nv = E1 - e0;                              // valid events (uniform)
             if (nv <= 0) return;
+            // the usual chunk: full, its arrivals within the ring and before m1
+            // whatever their slots.  An event's ring row before its slot, in
+            // bytes, comes from one lane of a vector (the kernel issues
+            // instructions in most of its cycles: what is uniform per event
+            // costs as much in scalar instructions as in vector ones)
+            if (nv >= KB) {
+                const int end = __builtin_amdgcn_readlane(stv, u8 + KB - 1);
+                if (end - f < TB && end + a.S <= m1) {
+                    const int bv = (fr - f + stv) * 256;
+                    int at[KB];
+                    float wv[KB];
+#pragma unroll
+                    for (int q = 0; q < KB; ++q) {
+                        const unsigned r = (unsigned)__builtin_amdgcn_readlane(bv, u8 + q) + (w[q].y << 8);
+                        at[q] = (int)min(r, r - (unsigned)(R * 256));   // row mod R (< 2 R)
+                        wv[q] = __uint_as_float(w[q].x);
+                    }
+                    ring_add(ring, at, wv);
+                    return;
+                }
+            }
             int st[KB];
 #pragma unroll
             for (int q = 0; q < KB; ++q) st[q] = __builtin_amdgcn_readlane(stv, u8 + q);
@@ -195,11 +248,11 @@ __global__ void __launch_bounds__(64) input_scan_kernel(InScanArgs a) {
                 for (int q = 0; q < KB; ++q) {
                     const int s = (int)w[q].y;
                     // uniform parts: the ring row of arrival step st[q], and
-                    // the slots that arrive before T (none past the end)
+                    // the slots that arrive before m1 (none past the end)
                     const int r0 = fr + (st[q] - f);
-                    const int lim = (q < nv) ? T - st[q] : 0;
+                    const int lim = (q < nv) ? m1 - st[q] : 0;
                     const unsigned r = (unsigned)(r0 + s);
-                    // an event past the end or arriving at or after T adds
+                    // an event past the end or arriving at or after m1 adds
                     // -0 (x + -0 = x exactly, signed zeros included) to its
                     // row, which lies in the lane's own ring window
                     row[q] = (int)min(r, r - (unsigned)R);     // r mod R (r < 2 R)
@@ -217,7 +270,7 @@ __global__ void __launch_bounds__(64) input_scan_kernel(InScanArgs a) {
                     const int s = (int)v[1];
                     int r = fr + s;
                     r = (r >= R) ? r - R : r;
-                    if (stq + s < T) ring[r * 64] = __fadd_rn(ring[r * 64], __uint_as_float((unsigned)v[0]));
+                    if (stq + s < m1) ring[r * 64] = __fadd_rn(ring[r * 64], __uint_as_float((unsigned)v[0]));
                 }
             }
         };
@@ -265,7 +318,7 @@ __global__ void __launch_bounds__(64) input_scan_kernel(InScanArgs a) {
             add_chunk(e0 + 5 * KB, stZ, KB, w2);
         }
     }
-    flush_to(T);
+    flush_to(m1);
 }
 
 // ------------------------------------------------------------------ readout
@@ -451,24 +504,33 @@ __global__ void __launch_bounds__(256) dmse_loss_kernel(const int* rec_cnt, cons
     loss_out[b] = (float)L;
 }
 
-// The batch mean of the per-sample losses, summed in sample order in fp64
-// from the fp64 values the per-sample kernel rounded to fp32 (one thread).
-__global__ void dmse_mean_kernel(const float* z, const int* labels, int B, int C, float delta,
-                                 float* loss_out, const DevStatus* st) {
-    if (st->bad_input || threadIdx.x != 0) return;
+// The batch mean of the per-sample losses, summed in sample order in fp64 from
+// the fp64 values the per-sample kernel rounded to fp32 (one workgroup: 256
+// samples' values at a time, each thread one, added by thread 0 in order).
+__global__ void __launch_bounds__(256) dmse_mean_kernel(const float* z, const int* labels, int B, int C, float delta,
+                                                        float* loss_out, const DevStatus* st) {
+    __shared__ double part[256];
+    if (st->bad_input) return;
     double tot = 0.0;
-    for (int b = 0; b < B; ++b) {
-        const int c = labels[b];
-        const float* zb = z + (size_t)b * C;
-        double L = 0.0;
-        for (int k = 0; k < C; ++k) {
-            if (k == c) continue;
-            const double e = (double)zb[k] - (double)zb[c] - (double)delta;
-            L += 0.5 * e * e;
+    for (int b0 = 0; b0 < B; b0 += 256) {
+        const int b = b0 + (int)threadIdx.x;
+        if (b < B) {
+            const int c = labels[b];
+            const float* zb = z + (size_t)b * C;
+            double L = 0.0;
+            for (int k = 0; k < C; ++k) {
+                if (k == c) continue;
+                const double e = (double)zb[k] - (double)zb[c] - (double)delta;
+                L += 0.5 * e * e;
+            }
+            part[threadIdx.x] = L;
         }
-        tot += L;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (int k = 0; k < min(256, B - b0); ++k) tot += part[k];
+        __syncthreads();
     }
-    loss_out[B] = (float)(tot / (double)B);
+    if (threadIdx.x == 0) loss_out[B] = (float)(tot / (double)B);
 }
 
 __global__ void zero_ints_kernel(int* p, long long n) {
@@ -557,8 +619,8 @@ hipError_t launch_round_delays(const float* const* D, const float* const* W, con
 
 hipError_t launch_input_scan(const InScanArgs& a, size_t lds, hipStream_t s) {
     const int nblk = (a.n1 + 63) / 64;
-    if (a.TB < 1 || a.S + a.TB - 1 < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(input_scan_kernel, dim3(a.B * nblk), dim3(64), lds, s, a);
+    if (a.TB < 1 || a.S + a.TB - 1 < 1 || a.segs < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(input_scan_kernel, dim3(a.B * nblk * a.segs), dim3(64), lds, s, a);
     return hipGetLastError();
 }
 
@@ -582,7 +644,7 @@ hipError_t launch_dmse_loss(const int* rec_cnt, const int* rec_s, const int* rec
                        B, C, T, dt, delta, z, loss_out, xlp, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(dmse_mean_kernel, dim3(1), dim3(64), 0, s, z, labels, B, C, delta, loss_out, st);
+    hipLaunchKernelGGL(dmse_mean_kernel, dim3(1), dim3(256), 0, s, z, labels, B, C, delta, loss_out, st);
     return hipGetLastError();
 }
 

@@ -752,7 +752,6 @@ void launch_f3(const CoreFwdArgs& a, bool rl, int threads, size_t lds, hipStream
 template <int MAXT>
 bool launch_ft(const CoreFwdArgs& a, int n_lif, int np, bool rl, int threads, size_t lds, hipStream_t s) {
     switch (n_lif * 4 + np) {
-        case 4 + 0: launch_f3<MAXT, 1, 0>(a, rl, threads, lds, s); return true;
         case 4 + 1: launch_f3<MAXT, 1, 1>(a, rl, threads, lds, s); return true;
         case 8 + 1: launch_f3<MAXT, 2, 1>(a, rl, threads, lds, s); return true;
         case 8 + 2: launch_f3<MAXT, 2, 2>(a, rl, threads, lds, s); return true;
@@ -767,7 +766,7 @@ bool launch_ft(const CoreFwdArgs& a, int n_lif, int np, bool rl, int threads, si
 template <int M, bool R, bool O>
 hipError_t set_lds_limits_t(size_t bytes, int* bad) {
     const void* fns[] = {
-        (const void*)forward_core_kernel<M, 1, 0, R, O>, (const void*)forward_core_kernel<M, 1, 1, R, O>,
+        (const void*)forward_core_kernel<M, 1, 1, R, O>,
         (const void*)forward_core_kernel<M, 2, 1, R, O>, (const void*)forward_core_kernel<M, 2, 2, R, O>,
         (const void*)forward_core_kernel<M, 3, 1, R, O>, (const void*)forward_core_kernel<M, 3, 2, R, O>,
         (const void*)forward_core_kernel<M, 4, 1, R, O>, (const void*)forward_core_kernel<M, 4, 2, R, O>};

@@ -75,7 +75,7 @@ struct ClusterArgs {
 // Input projection arrivals: A_in[b][n][j] = sum, in emission order, of the
 // input-projection weights arriving at post j of layer 1 at step n.
 struct InScanArgs {
-    int B, T, S, n_in, n1, TB;         // S: ring slots of the input projection; TB: step span
+    int B, T, S, n_in, n1, TB, segs;   // segs: segments of a trial; S: ring slots of the input projection; TB: step span
                                        // of an 8-event chunk on the fast path; the LDS ring
                                        // holds S + TB - 1 arrival steps
     const uint2* ws0;                  // input projection (weight bits, slot) [n_in][n1]
@@ -356,6 +356,8 @@ hipError_t launch_copy_state(const float* src, int stride, int off, int n, int B
 hipError_t launch_readout_adjoint(const ReadoutBwdArgs& a, int threads, size_t lds, hipStream_t s);
 hipError_t launch_backward_core(const CoreBwdArgs& a, int n_lif, int threads, size_t lds,
                                 hipStream_t s);
+hipError_t launch_forward_ff(const CoreFwdArgs& a, hipStream_t s);
+hipError_t launch_backward_ff(const CoreBwdArgs& a, hipStream_t s);
 int forward_split_head(int n_lif, int np, int nw, int* waves);
 hipError_t launch_split_tables(const SplitTables& a, hipStream_t s);
 hipError_t launch_forward_split(const CoreFwdArgs& a, int n_lif, int np, size_t lds, hipStream_t s);
@@ -364,7 +366,7 @@ hipError_t launch_backward_prep(const CoreBwdArgs& a, int n_lif, hipStream_t s);
 hipError_t launch_backward_split(const CoreBwdArgs& a, int n_lif, int np, size_t lds, hipStream_t s);
 bool backward_split_serves(int n_lif, int np, int maxn);
 hipError_t set_split_lds_limits(size_t bytes, int* bad);
-hipError_t launch_group(const GroupArgs& a, int B, hipStream_t s);
+hipError_t launch_group(const GroupArgs& a, int B, int threads, hipStream_t s);
 hipError_t launch_gradients(const GradArgs& a, int J, int KL, int threads, size_t lds, hipStream_t s);
 hipError_t launch_grad_reduce(const GradArgs& a, int P, hipStream_t s);
 hipError_t launch_optimizer(const OptArgs& a, hipStream_t s);
