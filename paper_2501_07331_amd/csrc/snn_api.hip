@@ -142,7 +142,8 @@ struct snn_net {
     long long in_gstep_cap;
     int* scratch;               // device address of the fixed scratch (snn_backward_noalloc)
     DevStatus* st;
-    DevStatus* st_host;         // pinned
+    DevStatus* st_host;         // pinned, and its device address
+    DevStatus* st_map;
     // the last forward's inputs, kept for the backward
     const float* W[SNN_MAXP];
     const int* in_off;
@@ -789,6 +790,7 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
     const char* what = "device allocation";
     int bad = -1;   // index of the kernel whose LDS limit was refused
     if (e == hipSuccess) e = hipHostMalloc((void**)&net->st_host, sizeof(DevStatus), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&net->st_map, net->st_host, 0);
     if (e == hipSuccess) {
         what = "scratch symbol address";
         e = scratch_address(&net->scratch);
@@ -831,8 +833,7 @@ extern "C" int snn_projection_info(const snn_net* net, int32_t p, int32_t* pre_l
 }
 
 static int read_status(snn_net* net) {
-    HIP_TRY(net, hipMemcpyAsync(net->st_host, net->st, sizeof(DevStatus), hipMemcpyDeviceToHost,
-                                net->stream));
+    HIP_TRY(net, launch_publish_status(net->st, net->st_map, net->stream));
     HIP_TRY(net, hipStreamSynchronize(net->stream));
     return SNN_OK;
 }
@@ -919,8 +920,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
     for (int k = K_SCAN; k < K_RADJ; ++k) net->ran[k] = 0;
     HIP_TRY(net, launch_reset_status(net->st, s));
     HIP_TRY(net, launch_validate(in->offsets, in->step, in->neuron, in->nnz, t.B, t.T, t.n_in, labels,
-                                 C, net->st, s));
-    HIP_TRY(net, launch_step_index(in->offsets, in->step, t.B, t.T, net->in_idx, net->st, s));
+                                 C, net->in_idx, net->st, s));
     HIP_TRY(net, launch_round_delays(D, W, t.woff, net->cnt, t.P, t.dmax, net->slot, net->ws,
                                      net->st, s));
 
@@ -1100,7 +1100,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
         const size_t li = (size_t)t.lif[t.out_l], B = t.B, cap = t.cap;
         HIP_TRY(net, launch_dmse_loss(net->rec_cnt + li * B, net->rec_s + li * B * cap,
                                       net->rec_n + li * B * cap, t.cap, labels, t.B, C, t.T, t.dt,
-                                      net->dmse_delta, net->z, loss, net->xlp_out, net->st, s));
+                                      net->dmse_delta, net->z, loss, net->xlp_out, z, net->st, s));
     } else {
         if (!net->ro_fused) {
             ReadoutArgs r{};
@@ -1120,10 +1120,8 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             TIMED(net, K_READ, launch_readout_forward(r, net->read_threads, net->lds_read, s));
         }
         HIP_TRY(net, launch_loss(net->z, labels, t.B, C, t.loss, t.rscale, net->tau_m, loss,
-                                 net->src, net->st, s));
+                                 net->src, z, net->st, s));
     }
-    if (z)
-        HIP_TRY(net, hipMemcpyAsync(z, net->z, sizeof(float) * t.B * C, hipMemcpyDeviceToDevice, s));
     int rc = read_status(net);
     if (rc) return rc;
     const DevStatus& h = *net->st_host;
@@ -1247,20 +1245,26 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
         r.tab_lds = net->radj_tab;
         TIMED(net, K_RADJ, launch_readout_adjoint(r, net->radj_threads, net->lds_radj, s));
     }
-    // spikes grouped by presynaptic neuron (inputs, then every LIF layer) on
-    // the second stream: they depend on the forward only, and run beside the
+    // spikes grouped by presynaptic neuron (inputs, then every LIF layer): they
+    // depend on the forward only, and run on the second stream beside the
     // latency-bound adjoint core (forked after the readout adjoint, whose
-    // workgroups take a whole CU's LDS); the gradients wait for them
-    const hipStream_t g_s = net->aux;
+    // workgroups take a whole CU's LDS); the gradients wait for them.  A
+    // feed-forward core is about as short as the two events cost: same stream
+    // (a whole step of 10-20-2, T = 100, B = 32: 118 us, on two streams 148; of
+    // 4-200-3, T = 600, B = 64: 354 against 364, with B = 256: 868 and 869).
+    const hipStream_t g_s = net->ff ? s : net->aux;
     // the split backward core's 16 waves leave a CU room (registers) for four
     // more: with 512 threads the grouping waited for the core's workgroups to end
     const int group_threads = net->split_H > 0 ? 256 : 512;
-    HIP_TRY(net, hipEventRecord(net->fork, s));
-    HIP_TRY(net, hipStreamWaitEvent(g_s, net->fork, 0));
+    if (g_s != s) {
+        HIP_TRY(net, hipEventRecord(net->fork, s));
+        HIP_TRY(net, hipStreamWaitEvent(g_s, net->fork, 0));
+    }
     net->ran[K_GROUP] = 1;
     if (net->timing) HIP_TRY(net, hipEventRecord(net->ev[2 * K_GROUP], g_s));
     {
-        GroupArgs g{};
+        GroupSet set{};
+        GroupArgs& g = set.g[set.n++];
         g.off = net->in_off;
         g.end = net->in_off;
         g.step = net->in_step;
@@ -1270,25 +1274,24 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
         g.g_step = in_gstep;
         g.stage_cap = (int)std::min<long long>(net->in_nnz, kGroupStage);
         g.st = net->st;
-        HIP_TRY(net, launch_group(g, t.B, group_threads, g_s));
-    }
-    for (int l = 1; l < t.L; ++l) {
-        if (t.kind[l] != SNN_LIF) continue;
-        const size_t li = (size_t)t.lif[l];
-        GroupArgs g{};
-        g.cnt = net->rec_cnt + li * t.B;
-        g.off_stride = t.cap;
-        g.step = net->rec_s + li * t.B * t.cap;
-        g.neuron = net->rec_n + li * t.B * t.cap;
-        g.n = t.n[l];
-        g.g_off = net->rec_goff + li * t.B * (t.maxn + 1);
-        g.g_step = net->rec_gstep + li * gstep_stride(t.B, t.cap);
-        g.stage_cap = std::min(t.cap, kGroupStage);
-        g.st = net->st;
-        HIP_TRY(net, launch_group(g, t.B, group_threads, g_s));
+        for (int l = 1; l < t.L; ++l) {
+            if (t.kind[l] != SNN_LIF) continue;
+            const size_t li = (size_t)t.lif[l];
+            GroupArgs& q = set.g[set.n++];
+            q.cnt = net->rec_cnt + li * t.B;
+            q.off_stride = t.cap;
+            q.step = net->rec_s + li * t.B * t.cap;
+            q.neuron = net->rec_n + li * t.B * t.cap;
+            q.n = t.n[l];
+            q.g_off = net->rec_goff + li * t.B * (t.maxn + 1);
+            q.g_step = net->rec_gstep + li * gstep_stride(t.B, t.cap);
+            q.stage_cap = std::min(t.cap, kGroupStage);
+            q.st = net->st;
+        }
+        HIP_TRY(net, launch_group(set, t.B, group_threads, g_s));
     }
     if (net->timing) HIP_TRY(net, hipEventRecord(net->ev[2 * K_GROUP + 1], g_s));
-    HIP_TRY(net, hipEventRecord(net->join, g_s));
+    if (g_s != s) HIP_TRY(net, hipEventRecord(net->join, g_s));
     // extra jump numerators per LIF layer: the readout part of the jump sums
     // (the layer feeding an LI readout), the spike-time loss's terms (LIF
     // output layer), plus the caller's dl_p/dt
@@ -1385,7 +1388,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
             TIMED(net, K_BCORE,
                   launch_backward_core(a, t.n_lif, net->core_threads, net->lds_core_b, s));
     }
-    HIP_TRY(net, hipStreamWaitEvent(s, net->join, 0));
+    if (g_s != s) HIP_TRY(net, hipStreamWaitEvent(s, net->join, 0));
     GradArgs ga{};
     ga.B = t.B;
     ga.T = t.T;

@@ -30,6 +30,8 @@
 // jump sums, gradient sums): the adjoints are amplified through small jump
 // denominators I- - theta, and fp32 state there moves some gradients by
 // percents from the exact (fp64) result on the audio-sized networks.
+#include <algorithm>
+
 #include "snn_device.h"
 
 namespace {
@@ -1039,7 +1041,8 @@ __global__ void __launch_bounds__(64 * (1 + NL * NP)) backward_cluster_kernel(Co
 // device memory), each neuron's steps sorted (thread per neuron, insertion
 // sort: the spikes arrive in step order, so a neuron's list is nearly
 // sorted), then written out.
-__global__ void __launch_bounds__(512) group_kernel(GroupArgs a) {
+__global__ void __launch_bounds__(512) group_kernel(GroupSet set) {
+    const GroupArgs& a = set.g[blockIdx.y];
     if (a.st->bad_input) return;
     const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
     const int lane = tid & 63, wv = tid >> 6;
@@ -1486,10 +1489,15 @@ hipError_t backward_cluster_occupancy(int n_lif, int np, int threads, size_t lds
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, threads, lds);
 }
 
-hipError_t launch_group(const GroupArgs& a, int B, int threads, hipStream_t s) {
-    if (a.stage_cap < 0 || threads < 64 || threads > 512 || threads % 64) return hipErrorInvalidValue;
-    const size_t lds = sizeof(int) * ((size_t)a.n + 1 + 16) + sizeof(unsigned short) * (size_t)a.stage_cap;
-    hipLaunchKernelGGL(group_kernel, dim3(B), dim3(threads), lds, s, a);
+hipError_t launch_group(const GroupSet& a, int B, int threads, hipStream_t s) {
+    if (a.n < 1 || a.n > SNN_MAX_LIF + 1 || threads < 64 || threads > 512 || threads % 64) return hipErrorInvalidValue;
+    size_t lds = 0;
+    for (int k = 0; k < a.n; ++k) {
+        if (a.g[k].stage_cap < 0) return hipErrorInvalidValue;
+        lds = std::max(lds, sizeof(int) * ((size_t)a.g[k].n + 1 + 16) +
+                                sizeof(unsigned short) * (size_t)a.g[k].stage_cap);
+    }
+    hipLaunchKernelGGL(group_kernel, dim3(B, a.n), dim3(threads), lds, s, a);
     return hipGetLastError();
 }
 

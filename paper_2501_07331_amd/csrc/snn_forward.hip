@@ -24,9 +24,12 @@ __global__ void clear_abort_kernel(DevStatus* st) {
     if (threadIdx.x == 0) st->cl_abort = 0;
 }
 
-// One workgroup per sample: offsets, label, ranges, strict (step, neuron) order.
-__global__ void validate_kernel(const int* off, const int* step, const int* neuron, int nnz, int B,
-                                int T, int n_in, const int* labels, int C, DevStatus* st) {
+// One workgroup per sample: offsets, label, ranges, strict (step, neuron) order;
+// then, for a valid sample, idx[b][n] = its first input event with step >= n, n
+// = 0 .. T (an invalid one's is not read: every later kernel returns).
+__global__ void __launch_bounds__(1024) validate_kernel(const int* off, const int* step, const int* neuron, int nnz,
+                                                        int B, int T, int n_in, const int* labels, int C, int* idx,
+                                                        DevStatus* st) {
     const int b = blockIdx.x;
     const int lo = off[b], hi = off[b + 1];
     bool bad = false;
@@ -35,9 +38,9 @@ __global__ void validate_kernel(const int* off, const int* step, const int* neur
     if (lo < 0 || hi < lo || hi > nnz) bad = true;
     const int y = labels[b];
     if (y < 0 || y >= C) bad = true;
+    const int nt = blockDim.x;
     if (!bad) {
         // four events per thread and round, their loads issued together
-        const int nt = blockDim.x;
         for (int e0 = lo + (int)threadIdx.x; e0 < hi; e0 += 4 * nt) {
             int s[4], i[4], sp[4], ip[4];
 #pragma unroll
@@ -58,21 +61,22 @@ __global__ void validate_kernel(const int* off, const int* step, const int* neur
         }
     }
     if (bad) atomicOr(&st->bad_input, 1);
+    if (__syncthreads_or(bad)) return;
+    for (int n = threadIdx.x; n <= T; n += nt) {
+        int l = lo, h = hi;
+        while (l < h) {
+            const int mid = (l + h) >> 1;
+            if (step[mid] < n) l = mid + 1; else h = mid;
+        }
+        idx[(size_t)b * (T + 1) + n] = l;
+    }
 }
 
-// idx[b][n] = first input event of sample b with step >= n, n = 0 .. T.
-__global__ void step_index_kernel(const int* off, const int* step, int B, int T, int* idx,
-                                  const DevStatus* st) {
-    if (st->bad_input) return;
-    const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= (long long)B * (T + 1)) return;
-    const int b = (int)(g / (T + 1)), n = (int)(g % (T + 1));
-    int lo = off[b], hi = off[b + 1];
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (step[mid] < n) lo = mid + 1; else hi = mid;
-    }
-    idx[g] = lo;
+// The status block into host memory (mapped): a launch instead of a copy.
+__global__ void publish_status_kernel(const DevStatus* st, DevStatus* host) {
+    static_assert(sizeof(DevStatus) % 4 == 0, "copied as words");
+    const int i = threadIdx.x;
+    if (i < (int)(sizeof(DevStatus) / 4)) reinterpret_cast<int*>(host)[i] = reinterpret_cast<const int*>(st)[i];
 }
 
 struct RoundArgs {
@@ -427,8 +431,9 @@ __global__ void __launch_bounds__(1024) readout_forward_kernel(ReadoutArgs a) {
 // Softmax cross-entropy on z in fp64; loss_out[b], loss_out[B] = mean; the
 // per-step loss source on the readout adjoint src = s g / tau_m (sum) or
 // g / tau_m (max) in fp64, g = (softmax - onehot) / B rounded to fp32 first.
+// z_out: the caller's copy of z, or NULL.
 __global__ void loss_kernel(const float* z, const int* labels, int B, int C, int loss, float rscale,
-                            float tau_m, float* loss_out, double* src, const DevStatus* st) {
+                            float tau_m, float* loss_out, double* src, float* z_out, const DevStatus* st) {
     __shared__ double part[256];
     if (st->bad_input) return;
     double tot = 0.0;
@@ -444,6 +449,7 @@ __global__ void loss_kernel(const float* z, const int* labels, int B, int C, int
         loss_out[b] = (float)ce;
         tot += ce;
         for (int k = 0; k < C; ++k) {
+            if (z_out) z_out[(size_t)b * C + k] = zb[k];
             const double p = exp((double)zb[k] - lse);
             const float g = (float)((p - (k == y ? 1.0 : 0.0)) / (double)B);
             src[(size_t)b * C + k] = (loss == SNN_LOSS_CE_SUM)
@@ -470,7 +476,7 @@ __global__ void loss_kernel(const float* z, const int* labels, int B, int C, int
 __global__ void __launch_bounds__(256) dmse_loss_kernel(const int* rec_cnt, const int* rec_s,
                                                         const int* rec_n, int cap, const int* labels,
                                                         int B, int C, int T, float dt, float delta,
-                                                        float* z, float* loss_out, double* xlp,
+                                                        float* z, float* loss_out, double* xlp, float* z_out,
                                                         const DevStatus* st) {
     __shared__ int first[1024];
     if (st->bad_input) return;
@@ -487,6 +493,7 @@ __global__ void __launch_bounds__(256) dmse_loss_kernel(const int* rec_cnt, cons
     for (int k = tid; k < C; k += blockDim.x) {
         const int n0 = (first[k] < cap) ? rec_s[base + first[k]] : T;
         z[(size_t)b * C + k] = (float)((double)n0 * (double)dt);
+        if (z_out) z_out[(size_t)b * C + k] = z[(size_t)b * C + k];
     }
     __syncthreads();
     if (tid != 0) return;
@@ -585,18 +592,15 @@ hipError_t launch_clear_abort(DevStatus* st, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_validate(const int* off, const int* step, const int* neuron, int nnz, int B, int T,
-                           int n_in, const int* labels, int C, DevStatus* st, hipStream_t s) {
-    hipLaunchKernelGGL(validate_kernel, dim3(B), dim3(1024), 0, s, off, step, neuron, nnz, B, T, n_in,
-                       labels, C, st);
+hipError_t launch_publish_status(const DevStatus* st, DevStatus* host, hipStream_t s) {
+    hipLaunchKernelGGL(publish_status_kernel, dim3(1), dim3(64), 0, s, st, host);
     return hipGetLastError();
 }
 
-hipError_t launch_step_index(const int* off, const int* step, int B, int T, int* idx,
-                             const DevStatus* st, hipStream_t s) {
-    const long long n = (long long)B * (T + 1);
-    hipLaunchKernelGGL(step_index_kernel, dim3(grid_for(n, 256)), dim3(256), 0, s, off, step, B, T,
-                       idx, st);
+hipError_t launch_validate(const int* off, const int* step, const int* neuron, int nnz, int B, int T,
+                           int n_in, const int* labels, int C, int* idx, DevStatus* st, hipStream_t s) {
+    hipLaunchKernelGGL(validate_kernel, dim3(B), dim3(1024), 0, s, off, step, neuron, nnz, B, T, n_in,
+                       labels, C, idx, st);
     return hipGetLastError();
 }
 
@@ -630,18 +634,19 @@ hipError_t launch_readout_forward(const ReadoutArgs& a, int threads, size_t lds,
 }
 
 hipError_t launch_loss(const float* z, const int* labels, int B, int C, int loss, float rscale,
-                       float tau_m, float* loss_out, double* src, const DevStatus* st, hipStream_t s) {
+                       float tau_m, float* loss_out, double* src, float* z_out, const DevStatus* st,
+                       hipStream_t s) {
     hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, s, z, labels, B, C, loss, rscale, tau_m,
-                       loss_out, src, st);
+                       loss_out, src, z_out, st);
     return hipGetLastError();
 }
 
 hipError_t launch_dmse_loss(const int* rec_cnt, const int* rec_s, const int* rec_n, int cap,
                             const int* labels, int B, int C, int T, float dt, float delta, float* z,
-                            float* loss_out, double* xlp, const DevStatus* st, hipStream_t s) {
+                            float* loss_out, double* xlp, float* z_out, const DevStatus* st, hipStream_t s) {
     if (C > 1024 || cap < 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(dmse_loss_kernel, dim3(B), dim3(256), 0, s, rec_cnt, rec_s, rec_n, cap, labels,
-                       B, C, T, dt, delta, z, loss_out, xlp, st);
+                       B, C, T, dt, delta, z, loss_out, xlp, z_out, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(dmse_mean_kernel, dim3(1), dim3(256), 0, s, z, labels, B, C, delta, loss_out, st);

@@ -272,7 +272,8 @@ struct CoreBwdArgs {
                                        // positions [NL][64] int, abort flag)
 };
 
-// Spikes of each sample grouped by presynaptic neuron, in step order.
+// Spikes of each sample grouped by presynaptic neuron, in step order, for one
+// presynaptic layer.
 struct GroupArgs {
     const int* off;                    // spikes of sample b start at off[b] (absolute index)
     const int* end;                    // [B+1] off (CSR) if cnt is NULL
@@ -285,6 +286,10 @@ struct GroupArgs {
     unsigned short* g_step;            // steps (< 65536), grouped by neuron
     int stage_cap;                     // spikes of a sample staged in LDS (more: sorted in place)
     const DevStatus* st;
+};
+struct GroupSet {                      // the inputs and the LIF layers, one launch
+    int n;
+    GroupArgs g[SNN_MAX_LIF + 1];
 };
 
 // The projections into one post layer, for the gradient pass.
@@ -339,9 +344,8 @@ struct OptArgs {
 // Kernel launchers (snn_forward.hip, snn_backward.hip, snn_optim.hip).
 hipError_t launch_reset_status(DevStatus* st, hipStream_t s);
 hipError_t launch_validate(const int* off, const int* step, const int* neuron, int nnz, int B, int T,
-                           int n_in, const int* labels, int C, DevStatus* st, hipStream_t s);
-hipError_t launch_step_index(const int* off, const int* step, int B, int T, int* idx,
-                             const DevStatus* st, hipStream_t s);
+                           int n_in, const int* labels, int C, int* idx, DevStatus* st, hipStream_t s);
+hipError_t launch_publish_status(const DevStatus* st, DevStatus* host, hipStream_t s);
 hipError_t launch_round_delays(const float* const* D, const float* const* W, const long long* woff,
                                const long long* cnt, int P, const int* dmax, uint8_t* slot, uint2* ws,
                                DevStatus* st, hipStream_t s);
@@ -350,7 +354,8 @@ hipError_t launch_forward_core(const CoreFwdArgs& a, int n_lif, int threads, siz
                                hipStream_t s);
 hipError_t launch_readout_forward(const ReadoutArgs& a, int threads, size_t lds, hipStream_t s);
 hipError_t launch_loss(const float* z, const int* labels, int B, int C, int loss, float rscale,
-                       float tau_m, float* loss_out, double* src, const DevStatus* st, hipStream_t s);
+                       float tau_m, float* loss_out, double* src, float* z_out, const DevStatus* st,
+                       hipStream_t s);
 hipError_t launch_copy_state(const float* src, int stride, int off, int n, int B, float* dst,
                              hipStream_t s);
 hipError_t launch_readout_adjoint(const ReadoutBwdArgs& a, int threads, size_t lds, hipStream_t s);
@@ -366,13 +371,13 @@ hipError_t launch_backward_prep(const CoreBwdArgs& a, int n_lif, hipStream_t s);
 hipError_t launch_backward_split(const CoreBwdArgs& a, int n_lif, int np, size_t lds, hipStream_t s);
 bool backward_split_serves(int n_lif, int np, int maxn);
 hipError_t set_split_lds_limits(size_t bytes, int* bad);
-hipError_t launch_group(const GroupArgs& a, int B, int threads, hipStream_t s);
+hipError_t launch_group(const GroupSet& a, int B, int threads, hipStream_t s);
 hipError_t launch_gradients(const GradArgs& a, int J, int KL, int threads, size_t lds, hipStream_t s);
 hipError_t launch_grad_reduce(const GradArgs& a, int P, hipStream_t s);
 hipError_t launch_optimizer(const OptArgs& a, hipStream_t s);
 hipError_t launch_dmse_loss(const int* rec_cnt, const int* rec_s, const int* rec_n, int cap,
                             const int* labels, int B, int C, int T, float dt, float delta, float* z,
-                            float* loss_out, double* xlp, const DevStatus* st, hipStream_t s);
+                            float* loss_out, double* xlp, float* z_out, const DevStatus* st, hipStream_t s);
 hipError_t launch_add_lp(double* dst, const double* base, const float* dlp, const double* nterm,
                          const int* rec_n, const int* cnt, int B, int cap, hipStream_t s);
 // Spike-count regulariser: per LIF layer l with rho[l] != 0 and neuron i,
