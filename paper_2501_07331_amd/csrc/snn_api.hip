@@ -728,7 +728,7 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
     ALLOC(net->rec_I, nl * B * cap);
     ALLOC(net->rec_idx, nl * B * T1);
     ALLOC(net->rec_cnt, nl * B);
-    if (net->split_f || net->split_H > 0) {
+    if (net->split_f || net->split_H > 0 || net->cl_f) {
         long long f = 0, q = 0;
         for (int p = 0; p < t.P; ++p) {
             if (t.pre[p] == 0 || t.kind[t.post[p]] != SNN_LIF) continue;
@@ -737,8 +737,8 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
             f += (long long)(t.n[t.pre[p]] + 1) * t.n[t.post[p]];
             q += t.n[t.post[p]];
         }
-        ALLOC(net->far, (size_t)f);
-        ALLOC(net->ffar, (size_t)f);
+        if (net->split_H > 0) ALLOC(net->far, (size_t)f);
+        if (net->split_f) ALLOC(net->ffar, (size_t)f);
         if (net->split_f && net->ro_fused) ALLOC(net->ro_far, (size_t)(t.n[feed] + 1) * C);
         ALLOC(net->post, (size_t)q * kPostCap);
         ALLOC(net->pcnt, (size_t)q);
@@ -924,8 +924,9 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
     HIP_TRY(net, launch_round_delays(D, W, t.woff, net->cnt, t.P, t.dmax, net->slot, net->ws,
                                      net->st, s));
 
-    if (net->split_f || net->split_H > 0) {
+    if (net->split_f || net->split_H > 0 || net->cl_f) {
         SplitTables st{};
+        st.post_slots = net->split_f ? 2 : 1;
         st.lif_total = t.lif_total;
         st.rowblocks = (t.lif_total + 7) / 8;
         for (int p = 0; p < t.P; ++p) {
@@ -933,8 +934,9 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             if (pre == 0 || t.kind[q] != SNN_LIF) continue;
             const int li = t.lif[pre];
             st.out[li][st.npost[li]++] = st.np;
-            st.pr[st.np++] = SplitProj{t.n[pre], t.n[q], t.Sp[p], net->ws + t.woff[p], net->far + net->foff[p],
-                                       net->ffar + net->foff[p],
+            st.pr[st.np++] = SplitProj{t.n[pre], t.n[q], t.Sp[p], net->ws + t.woff[p],
+                                       net->split_H > 0 ? net->far + net->foff[p] : nullptr,
+                                       net->split_f ? net->ffar + net->foff[p] : nullptr,
                                        net->post + net->poff[p] * kPostCap, net->pcnt + net->poff[p]};
         }
         for (int l = 1; l < t.L; ++l)
@@ -1019,6 +1021,8 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
                 y.ring[y.npost] = net->fring[p];
                 y.ws[y.npost] = net->ws + t.woff[p];
                 y.ffar[y.npost] = net->ffar + net->foff[p];
+                y.post[y.npost] = net->post + net->poff[p] * kPostCap;
+                y.pcnt[y.npost] = net->pcnt + net->poff[p];
                 ++y.npost;
             }
             for (int k = y.npost; k < 2; ++k) {

@@ -51,8 +51,8 @@ __device__ __forceinline__ void lds_barrier() {
 //      chunk's end, likewise; and its synapses of slot 0 for the backward core, projections then posts
 //      in order: the first kNearCap (weight bits; LDS byte offset of the post's
 //      fp64 ring column, projection << 16) and their number.
-//  the others: 64 posts of a projection each: the posts' synapses of slot 1,
-//      then slot 0, each in presynaptic order: the first kPostCap (weight bits;
+//  the others: 64 posts of a projection each: the posts' synapses of slot 1
+//      (where post_slots is 2), then slot 0, each in presynaptic order: the first kPostCap (weight bits;
 //      neuron, slot << 16) and their number.
 // The largest numbers go to the status block.
 __global__ void __launch_bounds__(512) split_tables_kernel(SplitTables a) {
@@ -76,9 +76,9 @@ __global__ void __launch_bounds__(512) split_tables_kernel(SplitTables a) {
                 const int pos = cnt + lanes_below(m);
                 const unsigned top = (unsigned)((p.S - 1) * nq);
                 if (j < nq) {
-                    p.far[k] = zero ? make_uint2(0u, top) : make_uint2(e.x, e.y * (unsigned)nq);
-                    p.ffar[k] = e.y < 2 ? make_uint2(0u, top * 4u) : make_uint2(e.x, e.y * (unsigned)(nq * 4));
-                    if (i == p.npre - 1) p.ffar[(size_t)p.npre * nq + j] = make_uint2(0u, top * 4u);
+                    if (p.far) p.far[k] = zero ? make_uint2(0u, top) : make_uint2(e.x, e.y * (unsigned)nq);
+                    if (p.ffar) p.ffar[k] = e.y < 2 ? make_uint2(0u, top * 4u) : make_uint2(e.x, e.y * (unsigned)(nq * 4));
+                    if (p.ffar && i == p.npre - 1) p.ffar[(size_t)p.npre * nq + j] = make_uint2(0u, top * 4u);
                 }
                 if (zero && pos < kNearCap)
                     a.near[(size_t)g * kNearCap + pos] = make_uint2(e.x, (unsigned)(j * 8) | ((unsigned)pp << 16));
@@ -110,7 +110,7 @@ __global__ void __launch_bounds__(512) split_tables_kernel(SplitTables a) {
 #pragma unroll 8
     for (int i = i0; i < i1; ++i) {
         const unsigned sl = p.ws[(size_t)i * nq + jc].y;
-        cnt[0] += sl == 1;
+        cnt[0] += sl == 1 && a.post_slots > 1;
         cnt[1] += sl == 0;
     }
     part[0][wave][lane] = cnt[0];
@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(512) split_tables_kernel(SplitTables a) {
 #pragma unroll 8
             for (int i = i0; i < i1; ++i) {
                 const uint2 e = p.ws[(size_t)i * nq + jc];
-                if (e.y < 2) {
+                if (e.y < a.post_slots) {
                     const int at = e.y ? pos[0]++ : pos[1]++;
                     if (at < kPostCap) out[at] = make_uint2(e.x, (unsigned)i | (e.y << 16));
                 }

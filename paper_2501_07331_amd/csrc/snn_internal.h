@@ -116,6 +116,8 @@ struct FwdLayer {
     int ring_lds[2];                   //   delay ring [S+1][nq] (row S: dummy): LDS float offset,
     float* ring[2];                    //   or the HBM ring [B][S+1][nq]
     const uint2* ws[2];                //   (weight bits, slot) [n][nq]
+    const uint2* post[2];              //   cluster mode: the posts' near synapses [nq][kPostCap]
+    const int* pcnt[2];                //   and their number [nq] (split_tables_kernel)
     const uint2* ffar[2];              //   split core: far table [n+1][nq] (split_tables_kernel)
     int* rec_n;                        // [B][cap] records: neuron, step, I-
     int* rec_s;
@@ -165,8 +167,8 @@ constexpr int kNearRegs = 8, kNearCap = 24, kPostCap = 32;
 struct SplitProj {
     int npre, nq, S;
     const uint2* ws;                   // (weight bits, slot) [npre][nq]
-    uint2* far;                        // [npre][nq] backward core
-    uint2* ffar;                       // [npre + 1][nq] forward core
+    uint2* far;                        // [npre][nq] backward core, or NULL
+    uint2* ffar;                       // [npre + 1][nq] forward core, or NULL
     uint2* post;                       // [nq][kPostCap]
     int* pcnt;                         // [nq]
 };
@@ -178,6 +180,7 @@ struct SplitTables {
     int ro_l;
     uint2* near;                       // [lif_total][kNearCap]
     int* ncnt;                         // [lif_total]
+    unsigned post_slots;               // slots below it are near for the forward core
     DevStatus* st;
 };
 
