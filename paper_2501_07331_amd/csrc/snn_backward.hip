@@ -642,8 +642,13 @@ struct BwdCluster {
     }
 
     // Weights and slots of spikes q < KC (ids in lanes q of `ids`) for post
-    // j of projection pp of layer l (rows clamped into the matrix).
-    static __device__ __forceinline__ void load_ws(const CoreBwdArgs& a, int l, int pp, int j, int ids,
+    // j of projection pp of layer l (rows clamped into the matrix): in groups
+    // of four, as many as hold the nr (uniform) spikes.  (The loads share the
+    // CU's memory path with the neuron wave's exchange: with all KC rows loaded
+    // in every step the core of two recurrent layers of 1024, T = 1000, batch
+    // 256, took 180 ms, now 162; that of a recurrent layer of 300, T = 500,
+    // batch 50, 966 us, now 850.)
+    static __device__ __forceinline__ void load_ws(const CoreBwdArgs& a, int l, int pp, int j, int ids, int nr,
                                                    uint2 (&w)[KC]) {
         const BwdLayer& y = a.ly[l];
         const int nq = y.nq[pp], rmax = y.npre[pp] - 1;
@@ -651,10 +656,14 @@ struct BwdCluster {
             (void*)y.ws[pp], (short)0, y.npre[pp] * nq * 8, 0x00020000);
         const int col8 = min(j, nq - 1) * 8;
 #pragma unroll
-        for (int q = 0; q < KC; ++q) {
-            const int r = min(max(__builtin_amdgcn_readlane(ids, q), 0), rmax);
-            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, col8, r * nq * 8, 0);
-            w[q] = make_uint2((unsigned)v[0], (unsigned)v[1]);
+        for (int q0 = 0; q0 < KC; q0 += 4) {
+            if (nr <= q0) break;
+#pragma unroll
+            for (int q = q0; q < q0 + 4; ++q) {
+                const int r = min(max(__builtin_amdgcn_readlane(ids, q), 0), rmax);
+                const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, col8, r * nq * 8, 0);
+                w[q] = make_uint2((unsigned)v[0], (unsigned)v[1]);
+            }
         }
     }
 
@@ -704,7 +713,7 @@ struct BwdCluster {
             if (rd > 0 && nr > 0) {
                 // spikes past the prefetched ones: ids, then weights, now
                 const int idr = load_id(a, P, l, ri, cnt, q0);
-                load_ws(a, l, pp, j, idr, wc);
+                load_ws(a, l, pp, j, idr, nr, wc);
             }
             // (unrolled over the KC slots, so that the weights stay in
             // registers; chunks past the round's spikes are skipped)
@@ -740,13 +749,16 @@ struct BwdCluster {
         int2 c3[NL];
 #pragma unroll
         for (int m = 0; m < NL; ++m) c3[m] = load_cr(P, m, max(n - 3, 0));
-        int i2 = 0;
+        int i2 = 0, n1 = 0;
+#pragma unroll
+        for (int m = 0; m < NL; ++m)
+            if (m == l) n1 = __builtin_amdgcn_readfirstlane(st.c1[m].x);
 #pragma unroll
         for (int m = 0; m < NL; ++m)
             if (m == l)
                 i2 = load_id(a, P, l, __builtin_amdgcn_readfirstlane(st.c2[m].y),
                              __builtin_amdgcn_readfirstlane(st.c2[m].x), 0);
-        if (n > 0) load_ws(a, l, pp, j, st.i1, wn);
+        if (n > 0) load_ws(a, l, pp, j, st.i1, n1, wn);
 #pragma unroll
         for (int m = 0; m < NL; ++m) {
             st.cn[m] = __builtin_amdgcn_readfirstlane(st.c1[m].x);
@@ -771,20 +783,21 @@ struct BwdCluster {
             st.c2[m] = load_cr(P, m, max(T - 3, 0));
         }
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        int i0 = 0;
+        int i0 = 0, n0 = 0;
 #pragma unroll
         for (int m = 0; m < NL; ++m) {
             st.cn[m] = __builtin_amdgcn_readfirstlane(c0[m].x);
             st.rn[m] = __builtin_amdgcn_readfirstlane(c0[m].y);
             if (m == l) {
-                i0 = load_id(a, P, l, st.rn[m], st.cn[m], 0);
+                n0 = st.cn[m];
+                i0 = load_id(a, P, l, st.rn[m], n0, 0);
                 st.i1 = load_id(a, P, l, __builtin_amdgcn_readfirstlane(st.c1[m].y),
                                 __builtin_amdgcn_readfirstlane(st.c1[m].x), 0);
             }
         }
         __builtin_amdgcn_s_waitcnt(kWaitVm0);
         uint2 wa[KC], wb[KC];
-        load_ws(a, l, pp, j, i0, wa);
+        load_ws(a, l, pp, j, i0, n0, wa);
         int n = T - 1;
         for (; n >= 1; n -= 2) {
             if (!gstep(a, P, g, r, l, pp, n, st, wa, wb)) return;
@@ -1028,8 +1041,9 @@ struct BwdCluster {
     }
 };
 
+// (at most 2 NL - 1 projections between LIF layers)
 template <int NL, int NP>
-__global__ void __launch_bounds__(64 * (1 + NL * NP)) backward_cluster_kernel(CoreBwdArgs a) {
+__global__ void __launch_bounds__(64 * (1 + (NP > 1 ? 2 * NL - 1 : NL))) backward_cluster_kernel(CoreBwdArgs a) {
     BwdCluster<NL, NP>::run(a);
 }
 
