@@ -8,7 +8,8 @@
 //                   steps in three passes), their trajectories, then the
 //                   readout part of the jump sum of every spike of the
 //                   feeding layer, computed in parallel over the spikes.
-//  backward_core    one workgroup per sample runs the LIF adjoints in reverse
+//  backward_core    (where the split and feed-forward cores do not serve) one
+//                   workgroup per sample runs the LIF adjoints in reverse
 //                   time.  The spikes of every step are known from the
 //                   forward's per-step masks, so the weights and slots of a
 //                   step's spikes, their I- and readout jump parts are

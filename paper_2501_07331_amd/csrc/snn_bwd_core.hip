@@ -32,6 +32,14 @@
 // them): instructions and above all branches that merely pass over an empty
 // step cost as much as its arithmetic.  Between two of them the neuron waves
 // run the free dynamics in a loop of its own, without barriers.
+//
+// Measured, 700-256-20 recurrent, T = 1000: the core 1232 -> 577 us at batch 256
+// (a workgroup per CU), 1170 -> 467 us at 32; the recurrent layer of 128, T =
+// 300, batch 128: 460 -> 196 us.  Two barriers a step with the slot 0 terms in
+// the helpers: 781; a loop over all steps: 796; four helpers instead of twelve:
+// 1043; the jump's factors by fp64 division in the helpers: 648.  Leaving out
+// the trajectory stores changes nothing: it is bound by the chain of LDS round
+// trips and two barriers' skew of a step with spikes, about 1200 cycles.
 #include "snn_device.h"
 
 namespace {
