@@ -39,7 +39,7 @@
 // the helpers: 781; a loop over all steps: 796; four helpers instead of twelve:
 // 1043; the jump's factors by fp64 division in the helpers: 648.  Leaving out
 // the trajectory stores changes nothing: it is bound by the chain of LDS round
-// trips and two barriers' skew of a step with spikes, about 1200 cycles.
+// trips of a step with spikes, about 1400 cycles.
 #include "snn_device.h"
 
 namespace {

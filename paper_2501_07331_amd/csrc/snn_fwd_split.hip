@@ -32,8 +32,9 @@
 // the two steps' spikes instead.
 //
 // Measured, 700-256-20 recurrent, T = 1000: the core with the readout 1063 -> 792
-// us at batch 256, 1042 -> 772 us at 32; T = 2000 at half the time step: 3248 ->
-// 2010 us; the recurrent layer of 128, T = 300, batch 128: 432 -> 286 us.  Bound
+// us at batch 256, 1042 -> 772 us at 32; T = 4000 at a quarter of the time step,
+// batch 64: 3248 -> 2010 us; the recurrent layer of 128, T = 300, batch 128: 432
+// -> 286 us.  Bound
 // by the ordered adds into the rings (without them 475 of 772 us; without the
 // readout wave 111 less).  Slot 0 alone kept near: 885; ring cells read four
 // together instead of two: 804 against 780; lists of 16 instead of 24 registers
