@@ -40,6 +40,7 @@
 // 1043; the jump's factors by fp64 division in the helpers: 648.  Leaving out
 // the trajectory stores changes nothing: it is bound by the chain of LDS round
 // trips of a step with spikes, about 1400 cycles.
+#include "snn_bwd_plan.h"
 #include "snn_device.h"
 
 namespace {
@@ -310,11 +311,13 @@ struct BwdSplit {
 
     // The barriers of active step n (gap: steps from the last active step, or
     // from step T, to it), the same for every wave:
-    //  - gap > run_max + 1: the jumps of the last active step have read its
+    //  - ring_lapped(gap - 1): the jumps of the last active step have read its
     //    ring row, which the free steps would overwrite;
     //  - gap > 1: row n + 1 is in, and the delayed sums of step n may read it
     //    (for gap 1 the last step's own barrier says so);
     //  - row n is in, and with LISTS the slots of step n.
+    // After the last active step, ring_lapped(n): its jumps have read its row,
+    // which the free steps down to step 0 would overwrite.
     static __device__ __forceinline__ void before_sums(const CoreBwdArgs& a, int gap) {
         if (gap > 1) lds_barrier();
     }
@@ -343,7 +346,7 @@ struct BwdSplit {
             }
             if (locate(h + u * a.H, s2, l, r)) id[u] = load_id(a, b, l, r);
         }
-        if (gap > a.run_max + 1) lds_barrier();
+        if (ring_lapped(gap - 1, a.run_max)) lds_barrier();
         before_sums(a, gap);
         // phase 1: terms of slots >= 1 (all terms in phase 2 where the slot-0
         // ones are the helpers')
@@ -415,6 +418,7 @@ struct BwdSplit {
                 help_step<LISTS>(a, b, h, lane, k + 1, K, last, B, s0, s1, s2, id0, id, X, Y);
         }
         if (k < K) help_step<LISTS>(a, b, h, lane, k, K, last, B, s0, s1, s2, id0, id, X, Y);
+        if (K > 0 && ring_lapped(last, a.run_max)) lds_barrier();
     }
 
     // ---- neuron waves
@@ -536,7 +540,7 @@ struct BwdSplit {
                 __builtin_amdgcn_s_waitcnt(kWaitVm0);
             }
             const int gap = last - s.n;
-            if (gap > a.run_max + 1) lds_barrier();
+            if (ring_lapped(gap - 1, a.run_max)) lds_barrier();
             for (int g = gap; g > 1; --g) free_step(a, j, L);
             before_sums(a, gap);
             free_step(a, j, L);
@@ -558,6 +562,7 @@ struct BwdSplit {
                 }
             }
         }
+        if (K > 0 && ring_lapped(last, a.run_max)) lds_barrier();
         for (int g = last; g > 0; --g) free_step(a, j, L);
         if (deg) atomicAdd(&a.st->degenerate, (unsigned long long)deg);
     }

@@ -1,0 +1,45 @@
+"""The split LIF cores where their waves run apart the farthest, against the
+oracle: the forward bit for bit, every dW and dD element within 1e-6 + 1e-4
+|ref| of its fp64 definition, finite, and the same bits in a second call."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from .gpu_util import assert_backward_close, assert_forward_bitexact, run_gpu, run_oracle
+from .test_gpu_core_splits import _lif, _net
+
+
+def _later(wl, steps):
+    """The same trials after `steps` silent steps."""
+    return dataclasses.replace(wl, cfg=dataclasses.replace(wl.cfg, T=wl.T + steps), T=wl.T + steps,
+                               in_step=(wl.in_step + steps).astype(np.int32))
+
+
+def _check(wl, silent=0, least=1.0, **kw):
+    orc = run_oracle(wl, modes=("f64",))
+    per = orc["fwd"].count.sum(axis=1) / (wl.B * np.array([n for n, k, _ in wl.cfg.layers if k == 1]))
+    first = min(int(orc["fwd"].step[l, b, 0]) for l in range(len(per)) for b in range(wl.B)
+                if orc["fwd"].count[l, b])
+    print(f"[edges] {wl.cfg.layers} T={wl.T} B={wl.B} spikes per neuron {per}, first at {first}", flush=True)
+    assert per.min() >= least and first >= silent
+    gpu = run_gpu(wl, **kw)
+    assert gpu["rc"] == 0
+    assert_forward_bitexact(gpu, orc, wl)
+    assert np.allclose(gpu["loss"], orc["loss"], rtol=1e-6, atol=1e-7)
+    assert all(np.isfinite(x).all() for x in gpu["dW"] + gpu["dD"])
+    assert_backward_close(gpu, orc)
+    again = run_gpu(wl, **kw)
+    for x, y in zip(gpu["dW"] + gpu["dD"], again["dW"] + again["dD"]):
+        assert np.array_equal(x.view(np.uint32), y.view(np.uint32)), "a second call differs"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("widths,high", [((100,), 4.0), ((100,), 6.0), ((130,), 8.0), ((256,), 1.0), ((70, 100), 6.0)])
+def test_steps_past_the_first_spikes(widths, high):
+    """More silent steps at the start of every trial than an adjoint ring has
+    rows, so that in reverse time the waves run past the last spikes' row while
+    another one may still read it; neurons with more synapses of slot 0 than
+    registers, and (1.0) with more than a list holds."""
+    rows = int(round(high)) + 1
+    _check(_later(_net(_lif(*widths), 90, 3, high), 5 * rows), silent=5 * rows)
