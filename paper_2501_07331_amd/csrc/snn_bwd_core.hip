@@ -28,6 +28,11 @@
 // zero throughout), the helpers take those terms too, between the step's
 // barrier and a second one.
 //
+// Terms that do not arrive are loaded with the others and have weight 0; the
+// cell that is loaded in their place (snn_bwd_plan.h: always one of the post
+// layer's ring, in a row that no wave writes meanwhile) may hold an infinity or
+// a NaN, so the high word of what it holds is cleared: 0 times a finite value.
+//
 // Both loops run over the steps that have spikes (backward_prep_kernel lists
 // them): instructions and above all branches that merely pass over an empty
 // step cost as much as its arithmetic.  Between two of them the neuron waves
@@ -187,10 +192,16 @@ struct BwdSplit {
         }
     }
 
+    // x where `in`, else a finite value (the high word cleared).
+    static __device__ __forceinline__ double finite_unless(bool in, double x) {
+        const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+        const unsigned hi = in ? (unsigned)(u >> 32) : 0u;
+        return __longlong_as_double((long long)(((unsigned long long)hi << 32) | (unsigned)u));
+    }
+
     // This lane's terms of slots >= 1 of one spike of layer l, subtracted from
     // v: the far table's weights times the ring cells of the arrivals (rows of
-    // steps past T - 1 were never written: zero; the table's entries of slot 0
-    // have weight 0).  nm: byte offset of the
+    // steps past T - 1 were never written: zero).  nm: byte offset of the
     // step's own row in each post ring.
     static __device__ __forceinline__ void far_terms(const CoreBwdArgs& a, const int (&nm)[NL][NP], int l, int lane,
                                                      const Row& R, double& v) {
@@ -202,16 +213,16 @@ struct BwdSplit {
             for (int pp = 0; pp < NP; ++pp) {
                 if (pp >= y.npost) continue;
                 const int nq = y.nq[pp];
-                const unsigned bytes = (unsigned)(y.qS[pp] * nq * 8);
+                const unsigned bytes = (unsigned)(y.qS[pp] * nq * 8), next = (unsigned)((nm[m][pp] + nq * 8));
                 const unsigned char* ring = smem + y.qring_lds[pp];
 #pragma unroll
                 for (int c0 = 0; c0 < MC; c0 += CH) {
                     double d[CH];
 #pragma unroll
                     for (int u = 0; u < CH; ++u) {
-                        const unsigned x = (unsigned)(nm[m][pp] + min((c0 + u) * 64 + lane, nq - 1) * 8) +
-                                           R.w[pp][c0 + u].y * 8u;
-                        d[u] = *(const lds_f64*)(ring + min(x, x - bytes));     // x < 2 rings
+                        const unsigned e = R.w[pp][c0 + u].y;
+                        const unsigned at = far_cell(next, (unsigned)min((c0 + u) * 64 + lane, nq - 1), e, bytes);
+                        d[u] = finite_unless(far_arrives(e), *(const lds_f64*)(ring + at));
                     }
 #pragma unroll
                     for (int u = 0; u < CH; ++u)
@@ -450,7 +461,8 @@ struct BwdSplit {
             N.most[l] = __builtin_amdgcn_readfirstlane(most);
 #pragma unroll
             for (int u = 0; u < kNearRegs; ++u) {
-                // an entry past the list: weight 0 of a valid cell
+                // an entry past the list: weight 0 of the first post's cell (a layer
+                // without LIF posts has no entries, and near_sum reads no cell)
                 const uint2 e = a.near[(size_t)i * kNearCap + u];
                 const bool in = u < N.cnt[l];
                 N.w[l][u] = in ? -(double)__uint_as_float(e.x) : 0.0;
@@ -469,10 +481,10 @@ struct BwdSplit {
         };
 #pragma unroll
         for (int u0 = 0; u0 < kNearRegs; u0 += 4) {
-            if (u0 > 0 && N.most[l] <= u0) break;
+            if (N.most[l] <= u0) break;
             double d[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) d[u] = cell(N.at[l][u0 + u]);
+            for (int u = 0; u < 4; ++u) d[u] = finite_unless(u0 + u < N.cnt[l], cell(N.at[l][u0 + u]));
 #pragma unroll
             for (int u = 0; u < 4; ++u) x = __fma_rn(N.w[l][u0 + u], d[u], x);
         }

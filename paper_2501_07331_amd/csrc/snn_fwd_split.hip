@@ -39,6 +39,7 @@
 // readout wave 111 less).  Slot 0 alone kept near: 885; ring cells read four
 // together instead of two: 804 against 780; lists of 16 instead of 24 registers
 // 2549 against 2010 (fine grid).
+#include "snn_bwd_plan.h"
 #include "snn_device.h"
 
 namespace {
@@ -52,8 +53,8 @@ __device__ __forceinline__ void lds_barrier() {
 
 // Tables of the LIF -> LIF projections, from their (weight, slot) pairs.
 //  workgroups [0, rowblocks): one wave per neuron i of the LIF layers: its
-//      rows of the far tables: of the backward core (far: weight bits, slot
-//      times nq) with slot 0, of the forward core (ffar [n + 1][nq]: weight
+//      rows of the far tables: of the backward core (far: weight bits, far_entry),
+//      of the forward core (ffar [n + 1][nq]: weight
 //      bits, slot times the bytes of a ring row) with slots 0 and 1 as weight +0
 //      at the largest slot (a cell that no pending step reads; a readout's
 //      table has all slots); row n of ffar, which stands in for spikes past a
@@ -85,7 +86,7 @@ __global__ void __launch_bounds__(512) split_tables_kernel(SplitTables a) {
                 const int pos = cnt + lanes_below(m);
                 const unsigned top = (unsigned)((p.S - 1) * nq);
                 if (j < nq) {
-                    if (p.far) p.far[k] = zero ? make_uint2(0u, top) : make_uint2(e.x, e.y * (unsigned)nq);
+                    if (p.far) p.far[k] = make_uint2(zero ? 0u : e.x, far_entry(e.y, (unsigned)nq));
                     if (p.ffar) p.ffar[k] = e.y < 2 ? make_uint2(0u, top * 4u) : make_uint2(e.x, e.y * (unsigned)(nq * 4));
                     if (p.ffar && i == p.npre - 1) p.ffar[(size_t)p.npre * nq + j] = make_uint2(0u, top * 4u);
                 }

@@ -1,6 +1,7 @@
-// The split backward core's schedule (csrc/snn_bwd_core.hip) over every small
-// case, on the CPU: what its waves read and write in the adjoint ring between
-// two barriers, by the rules that the kernel uses (csrc/snn_bwd_plan.h).
+// The split backward core's plan (csrc/snn_bwd_core.hip) over every small case,
+// on the CPU, by the rules that the kernel uses (csrc/snn_bwd_plan.h): what its
+// waves read and write in the adjoint ring between two barriers, and which cells
+// the terms of slots >= 1 read.
 // Argument "no-tail": without the meeting before the steps past the last spikes
 // (a planted mistake that has to be found).
 #include <cstdio>
@@ -58,6 +59,23 @@ int faults(int T, int S, const std::vector<int>& act, bool tail) {
     return bad;
 }
 
+// Every entry of a far table: the cell of its arrival, or, where nothing arrives
+// (slot 0, posts past the layer), one of the row after the spike's step.
+int wrong_cells(int S, int nq, int slots) {
+    const unsigned bytes = (unsigned)(S * nq * 8);
+    int bad = 0;
+    for (int n = 0; n < 2 * S; ++n)
+        for (int slot = -1; slot < slots; ++slot)            // -1: past the layer, loaded as 0
+            for (int j = 0; j < nq; ++j) {
+                const unsigned e = slot < 0 ? 0u : far_entry((unsigned)slot, (unsigned)nq);
+                const unsigned at = far_cell((unsigned)((n % S + 1) * nq * 8), (unsigned)j, e, bytes);
+                const bool arrives = slot > 0;
+                const unsigned want = (unsigned)(((n + (arrives ? slot : 1)) % S * nq + j) * 8);
+                bad += far_arrives(e) != arrives || at != want || at >= bytes;
+            }
+    return bad;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -80,6 +98,13 @@ int main(int argc, char** argv) {
                     bad += faults(T, S, n0 < n1 ? std::vector<int>{n1, n0} : std::vector<int>{n1}, tail) != 0;
                 }
     }
+    // (slots of a projection: up to the rows of its post layer's ring)
+    int cells = 0;
+    for (int S = 2; S <= 9; ++S)
+        for (int nq : {1, 3, 64, 70})
+            for (int slots = 1; slots <= S; ++slots) cells += wrong_cells(S, nq, slots);
+    cells += wrong_cells(256, 79, 256);
+    printf("%d wrong cells\n", cells);
     printf("%lld cases, %lld with a race\n", cases, bad);
-    return bad ? 1 : 0;
+    return bad || cells ? 1 : 0;
 }

@@ -1,5 +1,5 @@
-"""The split backward core's plan on the CPU: where its waves meet, for every
-small case (tests/bwd_plan_check.cpp, compiled with the header that the kernel
+"""The split backward core's plan on the CPU: where its waves meet and which ring
+cells they read, for every small case (tests/bwd_plan_check.cpp, compiled with the header that the kernel
 uses)."""
 import os
 import subprocess
@@ -23,8 +23,12 @@ def test_no_wave_overtakes_another_one_that_reads_the_ring(check):
     assert r.returncode == 0, r.stdout
 
 
+def test_terms_read_their_arrival_or_a_complete_row(check):
+    assert check().stdout.splitlines()[0] == "0 wrong cells"
+
+
 def test_the_check_finds_a_missing_meeting(check):
     """Without the barrier before the steps past the last spikes, a wave may
     write the row of those spikes again while another one reads it."""
     r = check("no-tail")
-    assert r.returncode == 1 and " 0 with a race" not in r.stdout, r.stdout
+    assert r.returncode == 1 and ", 0 with a race" not in r.stdout, r.stdout

@@ -6,8 +6,10 @@ import dataclasses
 import numpy as np
 import pytest
 
+from workloads import LOSS_DMSE
+
 from .gpu_util import assert_backward_close, assert_forward_bitexact, run_gpu, run_oracle
-from .test_gpu_core_splits import _lif, _net
+from .test_gpu_core_splits import N_IN, _lif, _net
 
 
 def _later(wl, steps):
@@ -43,3 +45,17 @@ def test_steps_past_the_first_spikes(widths, high):
     registers, and (1.0) with more than a list holds."""
     rows = int(round(high)) + 1
     _check(_later(_net(_lif(*widths), 90, 3, high), 5 * rows), silent=5 * rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,out,rec", [(200, 3, 0), (200, 3, 1), (70, 5, 0), (70, 5, 1), (64, 130, 0), (33, 1, 0)])
+def test_hidden_layer_and_first_spike_output(n, out, rec):
+    """A spiking output layer, which feeds no LIF layer: its jumps have no terms
+    of slot 0, whatever the LDS holds."""
+    _check(_net(((N_IN, 0, 0), (n, 1, rec), (out, 1, 0)), 120, 4, 20.0, loss=LOSS_DMSE))
+
+
+@pytest.mark.gpu
+def test_upper_layer_that_is_not_recurrent():
+    """Two hidden layers, the lower one recurrent."""
+    _check(_net(((N_IN, 0, 0), (100, 1, 1), (40, 1, 0), (5, 2, 0)), 90, 3, 6.0))
