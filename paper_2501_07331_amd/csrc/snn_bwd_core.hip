@@ -75,7 +75,8 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
 // have spikes of any LIF layer, last first (act), and their number; for every
 // record its jump's data: A2, k, r; the jump is lambda_V <- k lambda_V + r A
 // with r = 1 / (I- - theta), k = 1 + theta r, that is lambda_V + (theta
-// lambda_V + A) / (I- - theta); r < 0 marks a skipped one, I- <= theta.
+// lambda_V + A) / (I- - theta); r < 0 marks a skipped one, I- <= theta (r is 0 for
+// a current that has overflowed to infinity: a jump that changes nothing).
 __global__ void __launch_bounds__(256) backward_prep_kernel(CoreBwdArgs a, int nl) {
     const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x;
     for (int l = 0; l < nl; ++l) {
@@ -569,8 +570,8 @@ struct BwdSplit {
                     const JumpData q = slots(a, k)[a.ly[l].lif_off + j];
                     const double A = LISTS ? near_sum(a, N, l, j, s.nm[l][0], s.nm[l][NP - 1], q.A) : q.A;
                     const double v = __fma_rn(q.k, L.lv[l], __dmul_rn(q.r, A));
-                    L.lv[l] = q.r > 0.0 ? v : L.lv[l];
-                    deg += q.r > 0.0 ? 0 : 1;
+                    L.lv[l] = q.r >= 0.0 ? v : L.lv[l];
+                    deg += q.r >= 0.0 ? 0 : 1;
                 }
             }
         }

@@ -59,3 +59,22 @@ def test_hidden_layer_and_first_spike_output(n, out, rec):
 def test_upper_layer_that_is_not_recurrent():
     """Two hidden layers, the lower one recurrent."""
     _check(_net(((N_IN, 0, 0), (100, 1, 1), (40, 1, 0), (5, 2, 0)), 90, 3, 6.0))
+
+
+@pytest.mark.gpu
+def test_overflowed_currents_are_not_degenerate_jumps():
+    """Weights whose sums overflow: the neuron's current is infinite and it spikes
+    at every step, with jumps that change nothing and are not counted as skipped;
+    the gradients of the other neurons' synapses are as ever."""
+    wl = _net(_lif(70), 90, 3, 20.0)
+    wl.W[0][:, 0] = 3e38
+    orc = run_oracle(wl, modes=("f64",))
+    assert np.isinf(orc["fwd"].I_final).any()
+    gpu = run_gpu(wl)
+    assert_forward_bitexact(gpu, orc, wl)
+    dW64, dD64, deg = orc["f64"]
+    print(f"[edges] skipped jumps: {gpu['stats']['degenerate_jumps']}, oracle {deg}", flush=True)
+    assert gpu["stats"]["degenerate_jumps"] == deg
+    for g, r in zip(gpu["dW"] + gpu["dD"], dW64 + dD64):
+        g, r = np.asarray(g, np.float64)[:, 1:], r[:, 1:]
+        assert np.isfinite(r).all() and (np.abs(g - r) <= 1e-6 + 1e-4 * np.abs(r)).all()
