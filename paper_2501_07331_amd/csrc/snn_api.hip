@@ -119,7 +119,7 @@ struct snn_net {
     float* rec_I;
     int* rec_idx;
     int* rec_cnt;
-    unsigned long long* masks;  // [n_lif][B][T][core waves] spike masks
+    unsigned long long* masks;  // [n_lif][B][T][core waves] spike masks (split backward, ff cores)
     int* rec_goff;
     unsigned short* rec_gstep;
     float* z;
@@ -755,7 +755,7 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         ALLOC(net->act, B * T + B);
         ALLOC(net->jump, nl * B * cap);
     }
-    ALLOC(net->masks, nl * B * T * (size_t)nwaves);
+    if (net->ff || net->split_H > 0) ALLOC(net->masks, nl * B * T * (size_t)nwaves);
     ALLOC(net->rec_goff, nl * B * (t.maxn + 1));
     // (per layer a multiple of 8 entries, so that every layer starts 16-byte
     // aligned, and slack: the gradient pass copies the 16-bit lists as dwords)
@@ -1052,7 +1052,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             // (the split and feed-forward backward cores do not read the step table)
             y.steptab = net->ff || (net->split_f && net->split_H > 0)
                             ? nullptr : net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
-            y.masks = net->masks + li * B * (size_t)t.T * (net->core_threads / 64);
+            y.masks = net->masks ? net->masks + li * B * (size_t)t.T * (net->core_threads / 64) : nullptr;
             y.ncount = net->reg_on ? net->ncount + t.lif_off[l] : nullptr;
             y.out_count = records[li].count;
             y.out_step = records[li].step;
@@ -1390,6 +1390,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
         if (net->ff) {
             TIMED(net, K_BCORE, launch_backward_ff(a, s));
         } else if (net->split_H > 0) {
+            if (!net->split_f) HIP_TRY(net, launch_backward_masks(a, t.n_lif, s));
             HIP_TRY(net, launch_backward_prep(a, t.n_lif, s));
             TIMED(net, K_BCORE, launch_backward_split(a, t.n_lif, net->cl_np, net->lds_core_b, s));
         } else if (net->cl_b)

@@ -110,6 +110,21 @@ __global__ void __launch_bounds__(256) backward_prep_kernel(CoreBwdArgs a, int n
     if (lane == 0) a.nact[b] = cnt;
 }
 
+// The spike masks, from the records, where the forward core does not write them:
+// a workgroup takes 256 words of a sample's [T][NW] in layer blockIdx.y.
+__global__ void __launch_bounds__(256) backward_masks_kernel(CoreBwdArgs a) {
+    const int chunks = (a.T * a.NW + 255) / 256, b = (int)blockIdx.x / chunks;
+    const int k = ((int)blockIdx.x - b * chunks) * 256 + (int)threadIdx.x;
+    if (k >= a.T * a.NW) return;
+    const BwdLayer& y = a.ly[blockIdx.y];
+    const int n = k / a.NW, w = k - n * a.NW;
+    const int* idx = y.rec_idx + (size_t)b * (a.T + 1) + n;
+    const int* id = y.recn + (size_t)b * a.cap;
+    unsigned long long m = 0;
+    for (int r = idx[0]; r < idx[1]; ++r) m |= id[r] >> 6 == w ? 1ull << (id[r] & 63) : 0ull;
+    y.masks[(size_t)b * a.T * a.NW + k] = m;
+}
+
 // MC: 64-post chunks of the widest LIF-post layer, at most.
 template <int NL, int NP, int MC>
 struct BwdSplit {
@@ -624,6 +639,12 @@ const void* split_kernel(int n_lif, int np, int mc) {
 }
 
 }  // namespace
+
+hipError_t launch_backward_masks(const CoreBwdArgs& a, int n_lif, hipStream_t s) {
+    const int chunks = (a.T * a.NW + 255) / 256;
+    hipLaunchKernelGGL(backward_masks_kernel, dim3((unsigned)(a.B * chunks), n_lif), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_backward_prep(const CoreBwdArgs& a, int n_lif, hipStream_t s) {
     hipLaunchKernelGGL(backward_prep_kernel, dim3(a.B), dim3(256), 0, s, a, n_lif);

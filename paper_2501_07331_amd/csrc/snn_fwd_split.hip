@@ -648,7 +648,7 @@ struct FwdSplit {
                         y.rec_idx[(size_t)b * (T + 1) + n0 + lane] = idx[l];
 #pragma unroll
                         for (int k = 0; k < NWM; ++k)
-                            if (k < a.NW) y.masks[((size_t)b * T + n0 + lane) * a.NW + k] = mk[l][k];
+                            if (k < a.NW && y.masks) y.masks[((size_t)b * T + n0 + lane) * a.NW + k] = mk[l][k];
                     }
                 }
 #pragma unroll

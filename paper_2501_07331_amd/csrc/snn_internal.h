@@ -125,7 +125,8 @@ struct FwdLayer {
     int* rec_idx;                      // [B][T+1] first record of each step
     int* rec_cnt;                      // [B]
     int* steptab;                      // [B][T][SNN_STEP_ROW], or NULL (split core only)
-    unsigned long long* masks;         // [B][T][NW] spikes of each 64 neurons, one bit each
+    unsigned long long* masks;         // split, feed-forward cores: [B][T][NW] spikes of each 64
+                                       // neurons, one bit each
     int* ncount;                       // [n] spikes per neuron over the batch (added), or NULL
     int* out_count;                    // caller's records: [B], [B][cap], [B][cap]
     int* out_step;
@@ -249,7 +250,8 @@ struct BwdLayer {
     const int* recn;                   // [B][cap] neuron of the records
     const int* steptab;                // [B][T][SNN_STEP_ROW] per-step spike table
     const int* rec_idx;                // [B][T+1] first record of each step
-    const unsigned long long* masks;   // [B][T][NW] spikes of each 64 neurons, one bit each
+    unsigned long long* masks;         // split, feed-forward cores: [B][T][NW] spikes of each 64
+                                       // neurons, one bit each
     const double* A2;                  // [B][cap] extra jump numerator per record (the readout
                                        // part of the jump sums, spike-time loss terms), or NULL
 };
@@ -370,6 +372,7 @@ int forward_split_head(int n_lif, int np, int nw, int* waves);
 hipError_t launch_split_tables(const SplitTables& a, hipStream_t s);
 hipError_t launch_forward_split(const CoreFwdArgs& a, int n_lif, int np, size_t lds, hipStream_t s);
 hipError_t set_forward_split_lds_limits(size_t bytes, int* bad);
+hipError_t launch_backward_masks(const CoreBwdArgs& a, int n_lif, hipStream_t s);
 hipError_t launch_backward_prep(const CoreBwdArgs& a, int n_lif, hipStream_t s);
 hipError_t launch_backward_split(const CoreBwdArgs& a, int n_lif, int np, size_t lds, hipStream_t s);
 bool backward_split_serves(int n_lif, int np, int maxn);
