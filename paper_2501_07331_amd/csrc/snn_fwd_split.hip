@@ -27,9 +27,12 @@
 //  readout wave   the leaky-integrator readout fed by a LIF layer, if it fits
 //                 (an LDS ring of its own), one step late likewise.
 //
-// Where some neuron has more than kPostCap synapses of slots 0 and 1 (delays
-// near zero throughout), the neuron waves take them from the weight rows of
-// the two steps' spikes instead.
+// Where some neuron has more synapses of slots 0 and 1 than near_limit (delays
+// near zero throughout), the neuron waves take them from the weight rows of the
+// spikes instead, which they hold from one step to the next (dense_add: a step's
+// rows give its slot 0 at once and its slot 1 a step later).  T = 500, batch 128,
+// delays up to 5: 256 neurons 504 us, 128 362, 64 312 (both steps' rows loaded
+// in the step: 683, 481, 374; the general core 512, 405, 355).
 //
 // Measured, 700-256-20 recurrent, T = 1000: the core with the readout 1063 -> 792
 // us at batch 256, 1042 -> 772 us at 32; T = 4000 at a quarter of the time step,
@@ -173,6 +176,17 @@ struct FwdSplit {
     // memory in every step with spikes: delays drawn from 0 .. 50 give a neuron
     // 7.7 of them among 256, and the most of 256 neurons about 17)
     static constexpr int EN = NL == 1 && NWM == 4 ? 24 : 16;
+    // The longest lists taken synapse by synapse, with nw neuron waves: an entry
+    // past the registers costs a memory access in every step with spikes, the
+    // dense form one for every spike, and narrow layers have few.  T = 500, batch
+    // 128, recurrent layers, list against dense form: 64 neurons, lists of 31,
+    // 374 and 312 us; 128, 30, 381 and 359; 256, 31, 464 and 508; 300 (16
+    // registers), 26, 808 and 670, 20, 548 and 665.
+    // (Two layers of 100 and 60, 21 to 24: 432 and 444.)
+    static __device__ __forceinline__ int near_limit(int nw) {
+        return nw <= 2 ? (NL == 1 ? EN + 4 : EN + 8) : nw <= 4 ? kPostCap : EN + 8;
+    }
+    static_assert(EN + (EN < 24 ? 8 : 4) <= kPostCap, "the lists hold them");
     static constexpr int U = 2 * D;                  // steps that input arrivals are loaded ahead
     // spikes of a step whose rows are loaded a step ahead (as the registers allow)
     static constexpr int kRound = 2;                 // ring cells read together (see cells_add)
@@ -286,36 +300,81 @@ struct FwdSplit {
         return v;
     }
 
-    // The same from the weight rows of the two steps' spikes (n: the step).
-    static __device__ __forceinline__ float dense_add(const CoreFwdArgs& a, int j, int n, int l, int e, float v) {
-        const FwdLayer& y = a.ly[l];
-        const int nq = y.n, jc = min(j, nq - 1);
-#pragma unroll 1
-        for (int sl = n > 0 ? 1 : 0; sl >= 0; --sl) {
-            Spikes s;
-            spikes_of(n - sl, y.in_l[e], s);
-#pragma unroll 1
-            for (int r0 = 0; r0 < s.total; r0 += 64) {
-                const int ids = list_ids(s, n - sl, y.in_l[e], r0, 0);
-                const int m = min(64, s.total - r0);
-#pragma unroll 1
-                for (int k0 = 0; k0 < m; k0 += KB) {
-                    uint2 w[KB];
+    // The rows of a step's first HR spikes that a lane holds of one projection:
+    // the step's slot 0 is added from them, a step later its slot 1.
+    static constexpr int HR = NL == 1 ? 16 : 8;
+    struct Held {
+        Spikes s;
+        uint2 w[HR];
+    };
+
+    // Rows r0 .. r0 + KB (of the lane's ids; past the spikes: loaded, not used).
+    static __device__ __forceinline__ void dense_load(__amdgpu_buffer_rsrc_t rs, int col8, int row8, int ids, int r0,
+                                                      uint2* w) {
 #pragma unroll
-                    for (int k = 0; k < KB; ++k)
-                        w[k] = y.in_ws[e][(size_t)__builtin_amdgcn_readlane(ids, k0 + k) * nq + jc];
-#pragma unroll
-                    for (int k = 0; k < KB; ++k)
-                        v = __fadd_rn(v, k0 + k < m && w[k].y == (unsigned)sl ? __uint_as_float(w[k].x) : 0.0f);
-                }
-            }
+        for (int k = 0; k < KB; ++k) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, col8, __builtin_amdgcn_readlane(ids, r0 + k) * row8, 0);
+            w[k] = make_uint2((unsigned)v[0], (unsigned)v[1]);
         }
+    }
+    static __device__ __forceinline__ float dense_sum(const uint2* w, int left, unsigned slot, float v) {
+#pragma unroll
+        for (int k = 0; k < KB; ++k)
+            v = __fadd_rn(v, k < left && w[k].y == slot ? __uint_as_float(w[k].x) : 0.0f);
+        return v;
+    }
+
+    // The spikes of step n past the held ones, their rows loaded now.
+    static __device__ __forceinline__ float dense_rest(__amdgpu_buffer_rsrc_t rs, int col8, int row8, const Spikes& s,
+                                                       int n, int sl, unsigned slot, float v) {
+#pragma unroll 1
+        for (int r0 = HR; r0 < s.total; r0 += KB) {
+            uint2 x[KB];
+            dense_load(rs, col8, row8, list_ids(s, n, sl, r0, 0), 0, x);
+            v = dense_sum(x, s.total - r0, slot, v);
+        }
+        return v;
+    }
+
+    // x plus the same synapses, from the weight rows of the two steps' spikes (n:
+    // the step).
+    static __device__ __forceinline__ float dense_add(const CoreFwdArgs& a, int j, int n, int l, int e, Held& H,
+                                                      float v) {
+        const FwdLayer& y = a.ly[l];
+        const int nq = y.n, sl = y.in_l[e], col8 = min(j, nq - 1) * 8;
+        // (an argument indexed by a value that the compiler does not know makes it
+        // reload arguments within the loops instead of keeping them in scalar
+        // registers: one layer 303 us against 296, 12-128-27 recurrent, T = 300,
+        // batch 128; with two layers, which have none left, 264 against 285,
+        // 4-200-3 with a spiking output, T = 600, batch 256)
+        const int npre = NL == 1 ? nq : a.ly[sl].n;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)y.in_ws[e], (short)0, npre * nq * 8,
+                                                                            0x00020000);
+        const Spikes last = H.s;
+        uint2 w[HR];
+#pragma unroll
+        for (int k = 0; k < HR; ++k) w[k] = H.w[k];
+        spikes_of(n, sl, H.s);
+        if (H.s.total > 0) {
+            const int ids = list_ids(H.s, n, sl, 0, 0);
+#pragma unroll
+            for (int g = 0; g < HR; g += KB)
+                if (g == 0 || H.s.total > g) dense_load(rs, col8, nq * 8, ids, g, H.w + g);
+        }
+#pragma unroll
+        for (int g = 0; g < HR; g += KB)
+            if (last.total > g) v = dense_sum(w + g, last.total - g, 1u, v);
+        if (last.total > HR) v = dense_rest(rs, col8, nq * 8, last, n - 1, sl, 1u, v);
+#pragma unroll
+        for (int g = 0; g < HR; g += KB)
+            if (H.s.total > g) v = dense_sum(H.w + g, H.s.total - g, 0u, v);
+        if (H.s.total > HR) v = dense_rest(rs, col8, nq * 8, H.s, n, sl, 0u, v);
         return v;
     }
 
     template <bool DENSE>
     static __device__ __forceinline__ void step(const CoreFwdArgs& a, int j, int wave, int lane, int n, int par,
-                                                float ain, Lane& L) {
+                                                float ain, Lane& L, Held (&H)[NL][NP]) {
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
             const float gi = __fmul_rn(a.gamma, L.I[l]);
@@ -374,7 +433,7 @@ struct FwdSplit {
                 // the source layer: l itself, or l - 1 (a feed-forward projection)
                 const bool prev = l > 0 && y.in_l[e] != l;
                 if (prev ? on[l > 0 ? l - 1 : 0] | L.on[l > 0 ? l - 1 : 0] : on[l] | L.on[l])
-                    x[l][q] = DENSE ? dense_add(a, j, n, l, e, x[l][q]) : near_add(a, j, par, l, e, q, L, x[l][q]);
+                    x[l][q] = DENSE ? dense_add(a, j, n, l, e, H[l][q], x[l][q]) : near_add(a, j, par, l, e, q, L, x[l][q]);
                 L.I[l] = __fadd_rn(L.I[l], x[l][q]);
             }
         }
@@ -386,6 +445,11 @@ struct FwdSplit {
     static __device__ void neurons(const CoreFwdArgs& a, int b, int wave, int lane) {
         const int j = wave * 64 + lane, T = a.T;
         Lane L;
+        Held H[NL][NP];                                      // (used with DENSE only)
+#pragma unroll
+        for (int l = 0; l < NL; ++l)
+#pragma unroll
+            for (int q = 0; q < NP; ++q) H[l][q].s.total = 0;
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
             const FwdLayer& y = a.ly[l];
@@ -407,7 +471,7 @@ struct FwdSplit {
         gptr<const float> ain = (gptr<const float>)(a.A_in + (size_t)b * T * a.n1 + min(j, a.n1 - 1));
         if constexpr (DENSE) {
 #pragma unroll 1
-            for (int n = 0; n < T; ++n) step<true>(a, j, wave, lane, n, n & (D - 1), ain[(size_t)n * a.n1], L);
+            for (int n = 0; n < T; ++n) step<true>(a, j, wave, lane, n, n & (D - 1), ain[(size_t)n * a.n1], L, H);
         } else {
             // each step's arrival in a register of its own, reloaded for step n
             // + U as soon as it is used: no register moves while its load is in
@@ -421,13 +485,13 @@ struct FwdSplit {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const float v = x[u];
-                    step<false>(a, j, wave, lane, n0 + u, u & (D - 1), v, L);
+                    step<false>(a, j, wave, lane, n0 + u, u & (D - 1), v, L, H);
                     x[u] = ain[(size_t)min(n0 + U + u, T - 1) * a.n1];
                 }
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (n0 + u < T) step<false>(a, j, wave, lane, n0 + u, u & (D - 1), x[u], L);
+                if (n0 + u < T) step<false>(a, j, wave, lane, n0 + u, u & (D - 1), x[u], L, H);
         }
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
@@ -708,7 +772,7 @@ struct FwdSplit {
         if (a.st->bad_input) return;
         const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const bool dense = a.st->near_post > kPostCap;
+        const bool dense = a.st->near_post > near_limit(a.NW);
         // head and rings start at zero
         for (int k = tid * 4; k < a.ro_end; k += blockDim.x * 4) *(lds_u32*)(smem + k) = 0u;
         __syncthreads();

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from workloads import LOSS_DMSE
+from workloads.configs import projections
 
 from .gpu_util import assert_backward_close, assert_forward_bitexact, run_gpu, run_oracle
 from .test_gpu_core_splits import N_IN, _lif, _net
@@ -78,3 +79,25 @@ def test_overflowed_currents_are_not_degenerate_jumps():
     for g, r in zip(gpu["dW"] + gpu["dD"], dW64 + dD64):
         g, r = np.asarray(g, np.float64)[:, 1:], r[:, 1:]
         assert np.isfinite(r).all() and (np.abs(g - r) <= 1e-6 + 1e-4 * np.abs(r)).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("widths,high", [((64, 130), 1.0), ((256, 100), 1.0), ((256, 100), 6.0), ((33, 33), 0.0)])
+def test_near_synapses_between_feed_forward_layers(widths, high):
+    """Two layers, one projection between them, its smallest delays in lists over
+    their length (taken from the weight rows) and within it."""
+    _check(_net(_lif(*widths, rec=0), 90, 3, high))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("widths", [(64,), (200,), (300,)])
+@pytest.mark.parametrize("near", [15, 16, 17, 24, 25, 28, 29, 32, 33])
+def test_one_neuron_with_a_list_at_its_limits(widths, near):
+    """One neuron with this many recurrent synapses of slots 0 and 1 among longer
+    ones: lists that fill the registers, pass them, and pass what is taken from
+    lists at all."""
+    wl = _net(_lif(*widths), 90, 2, 6.0)
+    p = projections(wl.cfg.layers).index((1, 1))
+    wl.D[p][:] = np.float32(4.0)
+    wl.D[p][:near, 3] = np.arange(near, dtype=np.float32) % 2
+    _check(wl)
