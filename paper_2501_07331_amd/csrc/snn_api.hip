@@ -177,6 +177,38 @@ static int scan_segments(int T, int S, int waves, size_t lds, int n_cu) {
     return k;
 }
 
+// Which of two cores takes a batch in less time: the split one, or the general
+// one with its fewer waves and registers, of which a CU holds several.  In units
+// of the general core's time for a sample alone on a CU: it takes rounds of as
+// many samples as a CU holds, a round 0.04 + 0.055 per neuron wave longer for
+// every sample but the first (the ordered adds and sums of all share the CU's
+// LDS); the split core takes `one` a round.  Measured, T = 300, us at 1, 2, 3, 4
+// and 8 samples a CU (256 to 2048), split and general:
+//   forward   64 neurons   127 131 142 243 372     214 243 252 281 360
+//             128          156 295 432 570 1120    250 286 324 358 584
+//             256          283 532 826 1204 2390   328 408 492 672 1213
+//             300          362 690 1106 1474       728 949 1222 1755
+//             4-200-3      265 514 766 1022        650 734 840 957
+// (recurrent layers with their readouts, delays up to 25, 25, 30 and 40; 4-200-3
+// with a spiking output, T = 600.)
+static double general_time(long long k, int per_cu, int nw) {
+    const double more = 0.04 + 0.055 * nw;
+    auto round = [&](long long m) { return m > 0 ? 1.0 + (double)(m - 1) * more : 0.0; };
+    return (double)(k / per_cu) * round(per_cu) + round(k % per_cu);
+}
+
+// Workgroups of a kernel that a CU holds: a SIMD has 512 vector registers, given
+// out in eights, a workgroup's waves are dealt to the four SIMDs in turn, and
+// those of more than four waves all begin at the first (measured: two workgroups
+// of six waves with three waves of registers a SIMD run one after the other).
+static int blocks_per_cu(const void* f, int threads, size_t lds) {
+    hipFuncAttributes at{};
+    if (!f || hipFuncGetAttributes(&at, f) != hipSuccess) return 1;
+    const int waves = threads / 64, regs = std::max(8, (at.numRegs + 7) / 8 * 8), per = std::min(8, 512 / regs);
+    const int n = waves <= 4 ? 4 * per / waves : per / ((waves + 3) / 4);
+    return std::max<int>(1, (int)std::min<size_t>((size_t)n, kLds / std::max<size_t>(lds, 1)));
+}
+
 static int fail(snn_net* net, int code, const char* fmt, ...) {
     if (net) {
         va_list ap;
@@ -443,7 +475,10 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         // the split core: neuron waves, a scatter wave per 64 columns of every
         // ring, a record wave (and the readout's), its head of the LDS before
         // the rings; wherever the layers leave waves for all of them
-        // (700-256-20 recurrent, batch 256: 792 us, the general core 1063)
+        // (700-256-20 recurrent, batch 256: 792 us, the general core 1063) and
+        // the batch does not leave it several rounds that the general core takes
+        // in one (general_time; above four neuron waves, where the general core's
+        // readout is a kernel of its own, only from 385 neurons on)
         {
             int ns = 0, into[SNN_MAX_LAYERS] = {0};
             net->split_np = net->cl_np;
@@ -453,8 +488,24 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
                 net->split_np = std::max(net->split_np, ++into[t.post[p]]);
             }
             const int head = net->cl_np > 0 ? forward_split_head(t.n_lif, net->split_np, nwaves, &net->split_waves) : -1;
-            if (rings_lds && !(want_cl && coop && force_cl) && head >= 0 && nwaves + ns + 1 <= net->split_waves &&
-                align16(head) + used <= kLds) {
+            const int feed = t.pre[t.out_p];
+            const size_t ro = (size_t)(t.Sp[t.out_p] + 1) * C * sizeof(float);
+            const bool fits = rings_lds && !(want_cl && coop && force_cl) && head >= 0 &&
+                              nwaves + ns + 1 <= net->split_waves && align16(head) + used <= kLds;
+            bool faster = true;
+            if (fits && t.B > n_cu) {
+                const bool rw = !t.out_lif && feed != 0 && C <= 64;          // a readout wave
+                const long long k = (t.B + n_cu - 1) / n_cu;
+                const int sw = nwaves + ns + 1 + (rw && nwaves + ns + 2 <= net->split_waves ? 1 : 0);
+                const int per = blocks_per_cu(forward_split_fn(t.n_lif, net->split_np, nwaves), 64 * sw,
+                                              align16(head) + used + (rw ? ro : 0));
+                const bool grw = rw && nwaves <= 4;
+                const int gper = blocks_per_cu(forward_core_fn(t.n_lif, net->cl_np, nwaves, grw),
+                                               64 * (nwaves + (grw ? 1 : 0)), align16(used) + masks + (grw ? ro : 0));
+                const double one = nwaves > 4 ? 0.5 + 0.13 * (nwaves - 5) : (t.n_lif == 1 ? 0.5 : 0.36) + 0.08 * ns;
+                faster = (double)((k + per - 1) / per) * one <= general_time(k, gper, nwaves);
+            }
+            if (fits && faster) {
                 net->split_f = 1;
                 net->split_NS = ns;
                 for (int p = 0; p < t.P; ++p)

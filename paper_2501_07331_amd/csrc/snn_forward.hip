@@ -704,6 +704,10 @@ hipError_t launch_forward_core(const CoreFwdArgs& a, int n_lif, int threads, siz
     return hipGetLastError();
 }
 
+const void* forward_core_fn(int n_lif, int np, int nw, bool ro) {
+    return nw <= 4 ? forward_core_fn_256(n_lif, np, ro) : forward_core_fn_1024(n_lif, np);
+}
+
 hipError_t set_core_lds_limits(size_t bytes, int* bad) {
     hipError_t e = set_core_lds_limits_256(bytes, bad);
     if (e == hipSuccess) {

@@ -1,6 +1,10 @@
 // Forward core instantiations for workgroups of up to 1024 threads.
 #include "snn_fwd_core.h"
 
+const void* forward_core_fn_1024(int n_lif, int np) {
+    return n_lif == 1 && np == 1 ? (const void*)forward_core_kernel<1024, 1, 1, true, false> : nullptr;
+}
+
 bool launch_forward_core_1024(const CoreFwdArgs& a, int n_lif, int np, bool rl, int threads,
                              size_t lds, hipStream_t s) {
     return launch_ft<1024>(a, n_lif, np, rl, threads, lds, s);

@@ -1,6 +1,14 @@
 // Forward core instantiations for workgroups of up to 256 threads.
 #include "snn_fwd_core.h"
 
+const void* forward_core_fn_256(int n_lif, int np, bool ro) {
+    if (n_lif == 1 && np == 1)
+        return ro ? (const void*)forward_core_kernel<256, 1, 1, true, true> : (const void*)forward_core_kernel<256, 1, 1, true, false>;
+    if (n_lif == 2 && np == 1)
+        return ro ? (const void*)forward_core_kernel<256, 2, 1, true, true> : (const void*)forward_core_kernel<256, 2, 1, true, false>;
+    return nullptr;
+}
+
 bool launch_forward_core_256(const CoreFwdArgs& a, int n_lif, int np, bool rl, int threads,
                              size_t lds, hipStream_t s) {
     return launch_ft<256>(a, n_lif, np, rl, threads, lds, s);

@@ -824,6 +824,8 @@ int forward_split_head(int n_lif, int np, int nw, int* waves) {
     return f.f ? f.head : -1;
 }
 
+const void* forward_split_fn(int n_lif, int np, int nw) { return split_kernel(n_lif, np, nw).f; }
+
 hipError_t launch_split_tables(const SplitTables& a, hipStream_t s) {
     int blocks = a.rowblocks;
     for (int p = 0; p < a.np; ++p) blocks += (a.pr[p].nq + 63) / 64;

@@ -355,6 +355,12 @@ hipError_t launch_round_delays(const float* const* D, const float* const* W, con
                                const long long* cnt, int P, const int* dmax, uint8_t* slot, uint2* ws,
                                DevStatus* st, hipStream_t s);
 hipError_t launch_input_scan(const InScanArgs& a, size_t lds, hipStream_t s);
+// The kernels that serve a network of up to two LIF layers with rings in LDS
+// (nw: 64-neuron groups of the widest; ro: with a readout wave), NULL: none.
+const void* forward_core_fn_256(int n_lif, int np, bool ro);
+const void* forward_core_fn_1024(int n_lif, int np);
+const void* forward_core_fn(int n_lif, int np, int nw, bool ro);
+const void* forward_split_fn(int n_lif, int np, int nw);
 hipError_t launch_forward_core(const CoreFwdArgs& a, int n_lif, int threads, size_t lds,
                                hipStream_t s);
 hipError_t launch_readout_forward(const ReadoutArgs& a, int threads, size_t lds, hipStream_t s);
