@@ -71,6 +71,8 @@ struct snn_net {
     int bpart_off;              // backward-core LDS plan: partial jump sums or jump slots
     int split_H;                // helper waves of the split backward core (0: not used)
     int split_run;              // steps that its waves may run past a step's ring row
+    int bwd_general[3];         // the general backward core is the faster one nevertheless, by the most
+                                // synapses of slot 0 from a neuron (near_class)
     int ff;                     // one LIF layer that feeds no LIF layer: snn_ff_core.hip
     int split_f, split_NS, split_waves;   // the split forward core serves the network; its scatter
                                 // waves, and the most waves it may have
@@ -151,6 +153,7 @@ struct snn_net {
     const int* in_neuron;
     int in_nnz;
     int fwd_ok, fwd_overflow;
+    int fwd_near_pre;                  // its most synapses of slot 0 from a neuron (DevStatus)
     int timing;
     hipEvent_t ev[2 * K_N];
     snn_stats stats;
@@ -189,13 +192,23 @@ static int scan_segments(int T, int S, int waves, size_t lds, int n_cu) {
 //             256          283 532 826 1204 2390   328 408 492 672 1213
 //             300          362 690 1106 1474       728 949 1222 1755
 //             4-200-3      265 514 766 1022        650 734 840 957
-// (recurrent layers with their readouts, delays up to 25, 25, 30 and 40; 4-200-3
-// with a spiking output, T = 600.)
+//   backward  64            87 157 228 301 583     187 197 211 242 325
+//             128          106 197 290 388 754     240 283 312 355 770
+//             256          179 350 535 692 1323    383 486 841 1043 1803
+//             256, dense   347 666 994 1294 2441   381 479 798 930 1707
+//             300          344 665 1000 1289       732 1405 2078 2773
+//             4-200-3      248 433 646 860         536 648 769 1279
+// (recurrent layers with their readouts, delays up to 25, 25, 30 and 40; dense: up
+// to 2; 4-200-3 with a spiking output, T = 600.)
 static double general_time(long long k, int per_cu, int nw) {
     const double more = 0.04 + 0.055 * nw;
     auto round = [&](long long m) { return m > 0 ? 1.0 + (double)(m - 1) * more : 0.0; };
     return (double)(k / per_cu) * round(per_cu) + round(k % per_cu);
 }
+
+// The split backward core's times, by the most synapses of slot 0 from a neuron:
+// about the registers', longer lists, none (0, 1, 2).
+static int near_class(int near_pre) { return near_pre > kNearCap ? 2 : near_pre > 2 * kNearRegs ? 1 : 0; }
 
 // Workgroups of a kernel that a CU holds: a SIMD has 512 vector registers, given
 // out in eights, a workgroup's waves are dealt to the four SIMDs in turn, and
@@ -574,14 +587,35 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         const int KP = bwd_prefetch(NL);
         net->bpart_off = 0;
         // the split core (neuron waves and up to 12 helper waves) wherever the
-        // layers leave room for at least four helpers and have LIF -> LIF
+        // layers leave room for at least eight helpers and have LIF -> LIF
         // projections (700-256-20 recurrent: the general core 1232 us, with
-        // four helpers 1043, with twelve 577); its jump slots take the place of
-        // the partial sums
+        // four helpers 1043, with twelve 577; 700-768-20, four helpers, T = 500,
+        // batch 128: 3821 and 3353 in the general core), its jump slots taking
+        // the place of the partial sums, and its rings fit beside them
         const int H = std::min(12, 16 - nwaves);
-        const bool split = !hbm && net->cl_np > 0 && H >= 4 && backward_split_serves(t.n_lif, net->cl_np, maxlif);
-        const size_t part = split ? align16((size_t)2 * t.lif_total * sizeof(JumpData))
-                                  : align16((size_t)2 * NL * KP * 4 * nwaves * sizeof(double));
+        size_t rings = 0;
+        for (int l = 0; l < n_layers; ++l)
+            if (read_by_lif[l]) rings += align16((size_t)t.Sb[l] * t.n[l] * sizeof(double));
+        const size_t part_s = align16((size_t)2 * t.lif_total * sizeof(JumpData));
+        const size_t part_g = align16((size_t)2 * NL * KP * 4 * nwaves * sizeof(double));
+        bool split = !hbm && net->cl_np > 0 && H >= 8 && backward_split_serves(t.n_lif, net->cl_np, maxlif) &&
+                     part_s + rings <= kLds;
+        if (split && part_g + rings <= kLds) {
+            // (general_time; of the 256 neurons there, delays up to 10, lists of
+            // up to 24: 271 522 758 1010 1982 and 387 489 815 926 1711.  With the
+            // slot-0 sums in the helpers the core takes twice as long, and with
+            // eight helpers longer than the general one: 512 neurons, T = 500,
+            // batch 128, delays up to 10: 2384 and 1880)
+            const long long k = (t.B + n_cu - 1) / n_cu;
+            const double g = general_time(k, blocks_per_cu(backward_core_fn(t.n_lif, net->cl_np, nwaves), 64 * nwaves,
+                                                           part_g + rings), nwaves);
+            const double one[3] = {t.n_lif == 1 ? 0.47 : 0.36, t.n_lif == 1 ? 0.7 : 0.45,
+                                   t.n_lif > 1 ? 0.6 : H >= 12 ? 0.9 : H > 8 ? 0.95 : 1.27};
+            for (int c = 0; c < 3; ++c) net->bwd_general[c] = (double)k * one[c] > g;
+            split = !net->bwd_general[0];
+        }
+        // (the classes in order of their times: the last is the first to change)
+        const size_t part = split && net->bwd_general[2] ? std::max(part_s, part_g) : split ? part_s : part_g;
         size_t used = part;
         bool all_lds = !hbm;
         for (int l = 0; l < n_layers; ++l) {
@@ -1101,7 +1135,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             y.rec_idx = net->rec_idx + li * B * (size_t)(t.T + 1);
             y.rec_cnt = net->rec_cnt + li * B;
             // (the split and feed-forward backward cores do not read the step table)
-            y.steptab = net->ff || (net->split_f && net->split_H > 0)
+            y.steptab = net->ff || (net->split_f && net->split_H > 0 && !net->bwd_general[2])
                             ? nullptr : net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
             y.masks = net->masks ? net->masks + li * B * (size_t)t.T * (net->core_threads / 64) : nullptr;
             y.ncount = net->reg_on ? net->ncount + t.lif_off[l] : nullptr;
@@ -1214,6 +1248,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
     net->in_nnz = in->nnz;
     net->fwd_ok = 1;
     net->fwd_overflow = h.overflow;
+    net->fwd_near_pre = h.near_pre;
     if (h.overflow) return fail(net, SNN_EOVERFLOW, "a sample exceeded record_capacity spikes");
     return SNN_OK;
 }
@@ -1440,7 +1475,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
         a.nact = net->act + (size_t)t.B * t.T;
         if (net->ff) {
             TIMED(net, K_BCORE, launch_backward_ff(a, s));
-        } else if (net->split_H > 0) {
+        } else if (net->split_H > 0 && !net->bwd_general[near_class(net->fwd_near_pre)]) {
             if (!net->split_f) HIP_TRY(net, launch_backward_masks(a, t.n_lif, s));
             HIP_TRY(net, launch_backward_prep(a, t.n_lif, s));
             TIMED(net, K_BCORE, launch_backward_split(a, t.n_lif, net->cl_np, net->lds_core_b, s));

@@ -1446,6 +1446,20 @@ static bool launch_core_t(const CoreBwdArgs& a, int n_lif, int np, bool rl, int 
     }
 }
 
+template <int MAXT>
+static const void* core_fn_t(int n_lif, int np) {
+    switch (n_lif * 4 + np) {
+        case 4 + 1: return (const void*)backward_core_kernel<MAXT, 1, bwd_prefetch(1), 1, true>;
+        case 8 + 1: return (const void*)backward_core_kernel<MAXT, 2, bwd_prefetch(2), 1, true>;
+        case 8 + 2: return (const void*)backward_core_kernel<MAXT, 2, bwd_prefetch(2), 2, true>;
+        default: return nullptr;
+    }
+}
+
+const void* backward_core_fn(int n_lif, int np, int nw) {
+    return nw <= 4 ? core_fn_t<256>(n_lif, np) : core_fn_t<1024>(n_lif, np);
+}
+
 hipError_t launch_backward_core(const CoreBwdArgs& a, int n_lif, int threads, size_t lds,
                                 hipStream_t s) {
     if (n_lif < 1 || n_lif > SNN_MAX_LIF || threads != 64 * a.NW) return hipErrorInvalidValue;

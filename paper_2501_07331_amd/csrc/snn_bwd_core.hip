@@ -628,7 +628,7 @@ const void* split_kernel(int n_lif, int np, int mc) {
     if (n_lif == 1 && np == 1)
         return mc <= 2 ? (const void*)backward_split_kernel<1, 1, 2>
                : mc <= 4 ? (const void*)backward_split_kernel<1, 1, 4>
-               : mc <= 12 ? (const void*)backward_split_kernel<1, 1, 12> : nullptr;
+               : mc <= 8 ? (const void*)backward_split_kernel<1, 1, 8> : nullptr;
     if (n_lif == 2 && np == 1)
         return mc <= 2 ? (const void*)backward_split_kernel<2, 1, 2>
                : mc <= 4 ? (const void*)backward_split_kernel<2, 1, 4> : nullptr;
@@ -674,7 +674,7 @@ bool backward_split_serves(int n_lif, int np, int maxn) {
 }
 
 hipError_t set_split_lds_limits(size_t bytes, int* bad) {
-    static const int cases[7][3] = {{1, 1, 2}, {1, 1, 4}, {1, 1, 12}, {2, 1, 2}, {2, 1, 4}, {2, 2, 2}, {2, 2, 4}};
+    static const int cases[7][3] = {{1, 1, 2}, {1, 1, 4}, {1, 1, 8}, {2, 1, 2}, {2, 1, 4}, {2, 2, 2}, {2, 2, 4}};
     for (int k = 0; k < 7; ++k) {
         const hipError_t e = hipFuncSetAttribute(split_kernel(cases[k][0], cases[k][1], cases[k][2]),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);

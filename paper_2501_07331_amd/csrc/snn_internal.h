@@ -361,6 +361,7 @@ const void* forward_core_fn_256(int n_lif, int np, bool ro);
 const void* forward_core_fn_1024(int n_lif, int np);
 const void* forward_core_fn(int n_lif, int np, int nw, bool ro);
 const void* forward_split_fn(int n_lif, int np, int nw);
+const void* backward_core_fn(int n_lif, int np, int nw);
 hipError_t launch_forward_core(const CoreFwdArgs& a, int n_lif, int threads, size_t lds,
                                hipStream_t s);
 hipError_t launch_readout_forward(const ReadoutArgs& a, int threads, size_t lds, hipStream_t s);
