@@ -68,6 +68,7 @@ struct snn_net {
     int read_threads;           // readout workgroup size
     size_t lds_core_f, lds_core_b, lds_scan, lds_read, lds_grad, lds_radj;
     int mask_off, ids_off, scan_tb, scan_segs, table_lds;
+    int val_parts;              // workgroups a sample of the input validation
     int bpart_off;              // backward-core LDS plan: partial jump sums or jump slots
     int split_H;                // helper waves of the split backward core (0: not used)
     int split_run;              // steps that its waves may run past a step's ring row
@@ -670,6 +671,9 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         for (int l = 0; l < n_layers; ++l) t.bring[l] = net->bring_mode[l] >= 0 ? net->bring_mode[l] : -1;
         net->lds_core_b = used;
     }
+    // validation: at least 1024 steps a workgroup, no more workgroups than CUs
+    // (T = 4000, batch 64: 5.5 us, with one a sample 9.0)
+    net->val_parts = std::max(1, std::min((t.T + 1024) / 1024, n_cu / t.B));
     // input scan: windows of 128 arrival steps (a [128][64] table per wave)
     // input scan ring: S + TB - 1 arrival steps and a dummy row per 64-post
     // wave; TB as large as keeps four rings in one CU's LDS (40 KiB each),
@@ -1011,7 +1015,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
     for (int k = K_SCAN; k < K_RADJ; ++k) net->ran[k] = 0;
     HIP_TRY(net, launch_reset_status(net->st, s));
     HIP_TRY(net, launch_validate(in->offsets, in->step, in->neuron, in->nnz, t.B, t.T, t.n_in, labels,
-                                 C, net->in_idx, net->st, s));
+                                 C, net->in_idx, net->val_parts, net->st, s));
     HIP_TRY(net, launch_round_delays(D, W, t.woff, net->cnt, t.P, t.dmax, net->slot, net->ws,
                                      net->st, s));
 

@@ -24,13 +24,17 @@ __global__ void clear_abort_kernel(DevStatus* st) {
     if (threadIdx.x == 0) st->cl_abort = 0;
 }
 
-// One workgroup per sample: offsets, label, ranges, strict (step, neuron) order;
-// then, for a valid sample, idx[b][n] = its first input event with step >= n, n
-// = 0 .. T (an invalid one's is not read: every later kernel returns).
+// Offsets, label, ranges, strict (step, neuron) order of a sample; then idx[b][n]
+// = its first input event with step >= n, n = 0 .. T (an invalid one's is not
+// read: every later kernel returns; the search stays within the sample's events
+// whatever their order).  A sample's events and steps are dealt to `parts`
+// workgroups: where few samples have long trials one a sample would take their
+// steps, each a serial search, in many rounds on one CU (T = 65536, one sample:
+// 129 us with one, 7 with 64).
 __global__ void __launch_bounds__(1024) validate_kernel(const int* off, const int* step, const int* neuron, int nnz,
                                                         int B, int T, int n_in, const int* labels, int C, int* idx,
-                                                        DevStatus* st) {
-    const int b = blockIdx.x;
+                                                        int parts, DevStatus* st) {
+    const int b = (int)blockIdx.x / parts, part = (int)blockIdx.x - b * parts;
     const int lo = off[b], hi = off[b + 1];
     bool bad = false;
     if (b == 0 && lo != 0) bad = true;
@@ -38,14 +42,14 @@ __global__ void __launch_bounds__(1024) validate_kernel(const int* off, const in
     if (lo < 0 || hi < lo || hi > nnz) bad = true;
     const int y = labels[b];
     if (y < 0 || y >= C) bad = true;
-    const int nt = blockDim.x;
+    const int nt = blockDim.x * parts, t0 = part * (int)blockDim.x + (int)threadIdx.x;
     if (!bad) {
         // four events per thread and round, their loads issued together
-        for (int e0 = lo + (int)threadIdx.x; e0 < hi; e0 += 4 * nt) {
+        for (long long e0 = (long long)lo + t0; e0 < hi; e0 += 4ll * nt) {
             int s[4], i[4], sp[4], ip[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int e = min(e0 + u * nt, hi - 1), ep = max(e - 1, lo);
+                const int e = (int)min(e0 + (long long)u * nt, (long long)hi - 1), ep = max(e - 1, lo);
                 s[u] = step[e];
                 i[u] = neuron[e];
                 sp[u] = step[ep];
@@ -53,7 +57,7 @@ __global__ void __launch_bounds__(1024) validate_kernel(const int* off, const in
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int e = e0 + u * nt;
+                const long long e = e0 + (long long)u * nt;
                 if (e >= hi) continue;
                 if (s[u] < 0 || s[u] >= T || i[u] < 0 || i[u] >= n_in) bad = true;
                 if (e > lo && (long long)s[u] * n_in + i[u] <= (long long)sp[u] * n_in + ip[u]) bad = true;
@@ -62,7 +66,7 @@ __global__ void __launch_bounds__(1024) validate_kernel(const int* off, const in
     }
     if (bad) atomicOr(&st->bad_input, 1);
     if (__syncthreads_or(bad)) return;
-    for (int n = threadIdx.x; n <= T; n += nt) {
+    for (int n = t0; n <= T; n += nt) {
         int l = lo, h = hi;
         while (l < h) {
             const int mid = (l + h) >> 1;
@@ -598,9 +602,10 @@ hipError_t launch_publish_status(const DevStatus* st, DevStatus* host, hipStream
 }
 
 hipError_t launch_validate(const int* off, const int* step, const int* neuron, int nnz, int B, int T,
-                           int n_in, const int* labels, int C, int* idx, DevStatus* st, hipStream_t s) {
-    hipLaunchKernelGGL(validate_kernel, dim3(B), dim3(1024), 0, s, off, step, neuron, nnz, B, T, n_in,
-                       labels, C, idx, st);
+                           int n_in, const int* labels, int C, int* idx, int parts, DevStatus* st, hipStream_t s) {
+    if (parts < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(validate_kernel, dim3((unsigned)(B * parts)), dim3(1024), 0, s, off, step, neuron, nnz, B, T, n_in,
+                       labels, C, idx, parts, st);
     return hipGetLastError();
 }
 

@@ -349,7 +349,7 @@ struct OptArgs {
 // Kernel launchers (snn_forward.hip, snn_backward.hip, snn_optim.hip).
 hipError_t launch_reset_status(DevStatus* st, hipStream_t s);
 hipError_t launch_validate(const int* off, const int* step, const int* neuron, int nnz, int B, int T,
-                           int n_in, const int* labels, int C, int* idx, DevStatus* st, hipStream_t s);
+                           int n_in, const int* labels, int C, int* idx, int parts, DevStatus* st, hipStream_t s);
 hipError_t launch_publish_status(const DevStatus* st, DevStatus* host, hipStream_t s);
 hipError_t launch_round_delays(const float* const* D, const float* const* W, const long long* woff,
                                const long long* cnt, int P, const int* dmax, uint8_t* slot, uint2* ws,

@@ -114,3 +114,20 @@ def test_batches_of_several_samples_a_cu(layers, B, high):
     core serves with its slot-0 synapses in the lists and past them."""
     loss = LOSS_DMSE if layers[-1][1] == 1 else None
     _check(_net(layers, 24, B, high, d_in=3, drive=1.0, rate=0.1, loss=loss), least=0.2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,B", [(1023, 1), (1024, 1), (5000, 1), (3000, 3)])
+def test_long_trials_are_validated_to_their_last_event(T, B):
+    """Few samples with long trials, whose events and steps several workgroups
+    share; an event out of order or range anywhere is refused."""
+    import paper_2501_07331_amd as snn
+    wl = _net(_lif(5, rec=0), T, B, 1.0, drive=0.35, rate=0.01)
+    _check(wl)
+    n = len(wl.in_step)
+    for at in (0, n // 3, n - 1):
+        for what in ("in_step", "in_neuron"):
+            bad = dataclasses.replace(wl, **{what: getattr(wl, what).copy()})
+            getattr(bad, what)[at] = T if what == "in_step" else N_IN
+            with pytest.raises(snn.SNNError):
+                run_gpu(bad, backward=False)
