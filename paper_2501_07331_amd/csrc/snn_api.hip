@@ -86,8 +86,11 @@ struct snn_net {
     uint2* post;
     int* pcnt;
     long long foff[SNN_MAXP], poff[SNN_MAXP];   // a projection's offsets in far, pcnt (post: times kPostCap)
-    int* act;                   // backward: steps with spikes
-    JumpData* jump;             // [n_lif][B][cap]
+    // split backward core: steps with spikes, the records' jumps [n_lif][B][cap]: in the input arrivals' memory, which only the forward uses,
+    // or where they do not fit in bwd_mem
+    int* act;
+    double2* jump;
+    char* bwd_mem;
     int bring_mode[SNN_MAX_LAYERS];   // adjoint ring of a LIF layer: -2 none, -1 HBM, >= 0 LDS
                                       // byte offset
     int radj_threads, radj_tab;
@@ -249,8 +252,8 @@ static void free_all(snn_net* n) {
                     n->src,     n->Vf,      n->If,       n->table,     n->tr_lif, n->tr_out,
                     n->A2,       n->in_goff,   n->in_gstep, n->st,
                     n->gpart,   n->ws,      n->steptab, n->mom,   n->xlp_out, n->ncount,
-                    n->nterm,   n->clx,     n->masks, n->near, n->ncnt, n->act,
-                    n->far,     n->jump,  n->post,  n->pcnt, n->ffar,
+                    n->nterm,   n->clx,     n->masks, n->near, n->ncnt, n->bwd_mem,
+                    n->far,     n->post,  n->pcnt, n->ffar,
                     n->ro_far};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
@@ -597,7 +600,7 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         size_t rings = 0;
         for (int l = 0; l < n_layers; ++l)
             if (read_by_lif[l]) rings += align16((size_t)t.Sb[l] * t.n[l] * sizeof(double));
-        const size_t part_s = align16((size_t)2 * t.lif_total * sizeof(JumpData));
+        const size_t part_s = align16((size_t)2 * t.lif_total * sizeof(double2));
         const size_t part_g = align16((size_t)2 * NL * KP * 4 * nwaves * sizeof(double));
         bool split = !hbm && net->cl_np > 0 && H >= 8 && backward_split_serves(t.n_lif, net->cl_np, maxlif) &&
                      part_s + rings <= kLds;
@@ -810,7 +813,9 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
     if (e == hipSuccess) e = dalloc(&(ptr), (count));
     ALLOC(net->slot, (size_t)net->n_params);
     ALLOC(net->ws, (size_t)net->n_params);
-    ALLOC(net->steptab, nl * B * T * (size_t)SNN_STEP_ROW);
+    // (the step table is for the general and cluster backward cores)
+    const bool tab = !(net->ff || (net->split_f && net->split_H > 0 && !net->bwd_general[2]));
+    if (tab) ALLOC(net->steptab, nl * B * T * (size_t)SNN_STEP_ROW);
     ALLOC(net->in_idx, B * T1);
     ALLOC(net->A_in, B * T * t.n[1]);
     for (int p = 0; p < t.P; ++p)
@@ -841,8 +846,14 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
         ALLOC(net->ncnt, (size_t)t.lif_total);
     }
     if (net->split_H > 0) {
-        ALLOC(net->act, B * T + B);
-        ALLOC(net->jump, nl * B * cap);
+        const size_t jump = nl * B * cap * sizeof(double2), act = (B * T + B) * sizeof(int);
+        char* mem = (char*)net->A_in;
+        if (jump + act > B * T * t.n[1] * sizeof(float)) {
+            ALLOC(net->bwd_mem, jump + act);
+            mem = net->bwd_mem;
+        }
+        net->jump = (double2*)mem;
+        net->act = mem ? (int*)(mem + jump) : nullptr;
     }
     if (net->ff || net->split_H > 0) ALLOC(net->masks, nl * B * T * (size_t)nwaves);
     ALLOC(net->rec_goff, nl * B * (t.maxn + 1));
@@ -1138,9 +1149,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             y.rec_I = net->rec_I + li * B * cap;
             y.rec_idx = net->rec_idx + li * B * (size_t)(t.T + 1);
             y.rec_cnt = net->rec_cnt + li * B;
-            // (the split and feed-forward backward cores do not read the step table)
-            y.steptab = net->ff || (net->split_f && net->split_H > 0 && !net->bwd_general[2])
-                            ? nullptr : net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
+            y.steptab = net->steptab ? net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW : nullptr;
             y.masks = net->masks ? net->masks + li * B * (size_t)t.T * (net->core_threads / 64) : nullptr;
             y.ncount = net->reg_on ? net->ncount + t.lif_off[l] : nullptr;
             y.out_count = records[li].count;
@@ -1462,7 +1471,7 @@ static int backward_impl(snn_net* net, const float* const* dlp, float* const* dW
             y.jump = net->jump + li * B * cap;
             y.recI = net->rec_I + li * B * cap;
             y.recn = net->rec_n + li * B * cap;
-            y.steptab = net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW;
+            y.steptab = net->steptab ? net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW : nullptr;
             y.rec_idx = net->rec_idx + li * B * (size_t)(t.T + 1);
             y.masks = net->masks + li * B * (size_t)t.T * (net->core_threads / 64);
             y.A2 = jump_x[li];

@@ -38,11 +38,13 @@
 // step cost as much as its arithmetic.  Between two of them the neuron waves
 // run the free dynamics in a loop of its own, without barriers.
 //
-// Measured, 700-256-20 recurrent, T = 1000: the core 1232 -> 577 us at batch 256
-// (a workgroup per CU), 1170 -> 467 us at 32; the recurrent layer of 128, T =
-// 300, batch 128: 460 -> 196 us.  Two barriers a step with the slot 0 terms in
+// Measured, 700-256-20 recurrent, T = 1000: the core 1232 -> 539 us at batch 256
+// (a workgroup per CU), 1170 -> 440 us at 32; the recurrent layer of 128, T =
+// 300, batch 128: 460 -> 190 us.  Two barriers a step with the slot 0 terms in
 // the helpers: 781; a loop over all steps: 796; four helpers instead of twelve:
-// 1043; the jump's factors by fp64 division in the helpers: 648.  Leaving out
+// 1043; the jump's factors by fp64 division in the helpers: 648; with a jump's
+// factor of lambda_V, 24 bytes a record and slot, made beforehand: 577; its two
+// terms loaded apart: 582 (first-spike core of two layers 261).  Leaving out
 // the trajectory stores changes nothing: it is bound by the chain of LDS round
 // trips of a step with spikes, about 1400 cycles.
 #include "snn_bwd_plan.h"
@@ -73,10 +75,10 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
 
 // What the core needs of a call beside the records, per sample: the steps that
 // have spikes of any LIF layer, last first (act), and their number; for every
-// record its jump's data: A2, k, r; the jump is lambda_V <- k lambda_V + r A
-// with r = 1 / (I- - theta), k = 1 + theta r, that is lambda_V + (theta
-// lambda_V + A) / (I- - theta); r < 0 marks a skipped one, I- <= theta (r is 0 for
-// a current that has overflowed to infinity: a jump that changes nothing).
+// record the numerator's terms from elsewhere (A2) and r = 1 / (I- - theta) of its
+// jump lambda_V <- lambda_V + r (theta lambda_V + A); r < 0 marks a skipped one, I-
+// <= theta (r is 0 for a current that has overflowed to infinity: a jump that
+// changes nothing).
 __global__ void __launch_bounds__(256) backward_prep_kernel(CoreBwdArgs a, int nl) {
     const int tid = threadIdx.x, lane = tid & 63, b = blockIdx.x;
     for (int l = 0; l < nl; ++l) {
@@ -86,10 +88,7 @@ __global__ void __launch_bounds__(256) backward_prep_kernel(CoreBwdArgs a, int n
         for (int q = tid; q < cnt; q += 256) {
             // tau_m dV/dt just before the crossing is I- - theta (V- = theta)
             const double den = __dsub_rn((double)y.recI[r0 + q], a.theta), r = 1.0 / den;
-            JumpData* o = y.jump + r0 + q;
-            o->A = y.A2 ? y.A2[r0 + q] : 0.0;
-            o->k = __fma_rn(a.theta, r, 1.0);
-            o->r = den > 0.0 ? r : -1.0;
+            y.jump[r0 + q] = make_double2(y.A2 ? y.A2[r0 + q] : 0.0, den > 0.0 ? r : -1.0);
         }
     }
     if (tid >= 64) return;
@@ -137,10 +136,10 @@ struct BwdSplit {
     static constexpr int CH = MC < 4 ? MC : 4;               // chunks whose ring reads go out together
 
     // far-table rows of one spike (all its LIF-post projections, this lane's
-    // posts lane + 64 c) and its jump's data
+    // posts lane + 64 c) and its jump's A2 and r
     struct Row {
         uint2 w[NP][MC];
-        JumpData J;
+        double2 J;
     };
 
     // Position of spike q of a step (layers in order): layer l, record index
@@ -163,8 +162,10 @@ struct BwdSplit {
         return found;
     }
 
-    // (loads of uniform addresses through a per-lane zero that the compiler
-    // cannot see: scalar loads would count on the LDS counter)
+    // (Loads of uniform addresses through a per-lane zero that the compiler
+    // cannot see: scalar loads would count on the LDS counter.  The layers'
+    // records lie one after the other: one base for all, as scalar registers are
+    // short, 4-200-3 with a spiking output 252 us with one each, now 232.)
     static __device__ __forceinline__ int lane_zero() {
         int zero;
         asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
@@ -172,11 +173,7 @@ struct BwdSplit {
     }
 
     static __device__ __forceinline__ int load_id(const CoreBwdArgs& a, int b, int l, int r) {
-        int id = 0;
-#pragma unroll
-        for (int m = 0; m < NL; ++m)
-            if (m == l) id = (a.ly[m].recn + (size_t)b * a.cap + r)[lane_zero()];
-        return id;
+        return (a.ly[0].recn + ((size_t)l * a.B + b) * a.cap + r)[lane_zero()];
     }
 
     // Byte offsets of this lane's posts in a row of projection pp of layer l;
@@ -188,11 +185,11 @@ struct BwdSplit {
 
     static __device__ __forceinline__ void load_row(const CoreBwdArgs& a, int b, int l, int r, int id, int lane,
                                                     Row& R) {
+        R.J = (a.ly[0].jump + ((size_t)l * a.B + b) * a.cap + r)[lane_zero()];
 #pragma unroll
         for (int m = 0; m < NL; ++m) {
             if (m != l) continue;
             const BwdLayer& y = a.ly[m];
-            R.J = (y.jump + (size_t)b * a.cap + r)[lane_zero()];
 #pragma unroll
             for (int pp = 0; pp < NP; ++pp) {
                 if (pp >= y.npost) continue;
@@ -272,19 +269,19 @@ struct BwdSplit {
 
     // The slots of the spiking neurons, by neuron: the jump's data with the
     // sum so far.  [2 (parity of the active step's index)][lif_total].
-    static __device__ __forceinline__ JumpData* slots(const CoreBwdArgs& a, int k) {
-        return reinterpret_cast<JumpData*>(smem + a.slot_off) + (k & 1) * a.lif_total;
+    static __device__ __forceinline__ double2* slots(const CoreBwdArgs& a, int k) {
+        return reinterpret_cast<double2*>(smem + a.slot_off) + (k & 1) * a.lif_total;
     }
 
-    static __device__ __forceinline__ void put(const CoreBwdArgs& a, int k, int l, int id, int lane, const JumpData& J,
+    static __device__ __forceinline__ void put(const CoreBwdArgs& a, int k, int l, int id, int lane, const Row& R,
                                                double v) {
         int off = 0;
 #pragma unroll
         for (int m = 0; m < NL; ++m)
             if (m == l) off = a.ly[m].lif_off;
-        JumpData* s = slots(a, k) + off + id;
+        double2* s = slots(a, k) + off + id;
         const double x = wave_sum_f64(v);
-        if (lane == 63) *s = JumpData{J.A + x, J.k, J.r};
+        if (lane == 63) *s = make_double2(R.J.x + x, R.J.y);
     }
 
     // Active steps of the sample in blocks of 64, one per lane: the step, the
@@ -383,7 +380,7 @@ struct BwdSplit {
             if (!LISTS || !locate(h + u * a.H, s0, l, r)) break;
             double v = 0.0;
             far_terms(a, s0.nm, l, lane, cur[u], v);
-            put(a, k, l, id0[u], lane, cur[u].J, v);
+            put(a, k, l, id0[u], lane, cur[u], v);
         }
         // spikes past the first RW of every helper: loaded now
         if (LISTS && tot > RW * a.H) more<false>(a, b, h + RW * a.H, lane, k, s0, tot);
@@ -413,7 +410,7 @@ struct BwdSplit {
             double v = 0.0;
             if (NEAR) near_terms(a, s.nm, l, id, lane, v);
             far_terms(a, s.nm, l, lane, R, v);
-            put(a, k, l, id, lane, R.J, v);
+            put(a, k, l, id, lane, R, v);
         }
     }
 
@@ -582,11 +579,11 @@ struct BwdSplit {
                 const unsigned long long m = ((unsigned long long)hi << 32) | lo;
                 if (m == 0) continue;
                 if ((m >> lane) & 1ull) {
-                    const JumpData q = slots(a, k)[a.ly[l].lif_off + j];
-                    const double A = LISTS ? near_sum(a, N, l, j, s.nm[l][0], s.nm[l][NP - 1], q.A) : q.A;
-                    const double v = __fma_rn(q.k, L.lv[l], __dmul_rn(q.r, A));
-                    L.lv[l] = q.r >= 0.0 ? v : L.lv[l];
-                    deg += q.r >= 0.0 ? 0 : 1;
+                    const double2 q = slots(a, k)[a.ly[l].lif_off + j];
+                    const double A = LISTS ? near_sum(a, N, l, j, s.nm[l][0], s.nm[l][NP - 1], q.x) : q.x;
+                    const double v = __fma_rn(q.y, __fma_rn(a.theta, L.lv[l], A), L.lv[l]);
+                    L.lv[l] = q.y >= 0.0 ? v : L.lv[l];
+                    deg += q.y >= 0.0 ? 0 : 1;
                 }
             }
         }

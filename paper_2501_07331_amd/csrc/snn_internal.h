@@ -221,12 +221,6 @@ struct ReadoutBwdArgs {
     int tab_lds;                       // 1: the [T][C] table of lambda_I - lambda_V lives in LDS
 };
 
-// A recorded spike's jump lambda_V <- k lambda_V + r A (A: the numerator's sum
-// so far; r < 0: skipped).
-struct JumpData {
-    double A, k, r;
-};
-
 // One LIF layer as seen by the backward core.
 struct BwdLayer {
     int n, lif_off;
@@ -245,7 +239,7 @@ struct BwdLayer {
     double* qring[2];
     const uint2* ws[2];                //   (weight bits, slot) [n][nq]
     const uint2* far[2];               //   split core: far table [n][nq] (split_tables_kernel)
-    JumpData* jump;                    // split core: [B][cap]
+    double2* jump;                     // split core: [B][cap] A2 and 1 / (I- - theta) (< 0: skipped)
     const float* recI;                 // [B][cap] I- of the records
     const int* recn;                   // [B][cap] neuron of the records
     const int* steptab;                // [B][T][SNN_STEP_ROW] per-step spike table
@@ -264,7 +258,7 @@ struct CoreBwdArgs {
     DevStatus* st;
     int part_off;                      // LDS byte offset of the partial jump sums
     // split core: helper waves, LDS byte offset of the jump slots
-    // ([2][lif_total] JumpData), steps that a wave may run past a step's row in
+    // ([2][lif_total]: A so far and r), steps that a wave may run past a step's row in
     // the rings, the synapses of slot 0 (split_tables_kernel)
     int H, slot_off, run_max;
     const uint2* near;

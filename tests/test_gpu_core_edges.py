@@ -131,3 +131,31 @@ def test_long_trials_are_validated_to_their_last_event(T, B):
             getattr(bad, what)[at] = T if what == "in_step" else N_IN
             with pytest.raises(snn.SNNError):
                 run_gpu(bad, backward=False)
+
+
+@pytest.mark.gpu
+def test_device_memory_of_a_handle():
+    """A record slot costs a handle its record (12 bytes), its grouped step (2) and
+    its readout jump term (8); a step the arrivals, the trajectories, the spike
+    masks and two indices: nothing beside them that only one core uses."""
+    import torch
+    import paper_2501_07331_amd as snn
+    B, n, C = 256, 256, 20
+
+    def used(T, cap):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        net = snn.Network([(100, 0, 0), (n, 1, 1), (C, 2, 0)], 20.0, 5.0, 1.0, 1.0, 50, B, T, snn.SNN_LOSS_CE_SUM,
+                          1.0 / T, cap, proj_max_delay=[50, 50, 50])
+        x = free - torch.cuda.mem_get_info()[0]
+        net.close()
+        return x
+
+    used(100, 64)
+    slack = 24 << 20                                     # allocations in steps of 2 MiB
+    base = used(500, 64)
+    a, b = used(500, 64 * n) - base, used(1000, 64) - base
+    per_record, per_step = 12 + 2 + 8, 4 * n + 16 * (n + C) + 8 * n // 64 + 8
+    print(f"[edges] bytes a record {a / (B * 64 * (n - 1))}, a step {b / (B * 500)}", flush=True)
+    assert a <= per_record * B * 64 * (n - 1) + slack
+    assert b <= per_step * B * 500 + slack
