@@ -1092,6 +1092,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             if (t.kind[l] != SNN_LIF) continue;
             const int li = t.lif[l];
             FwdLayer& y = a.ly[li];
+            FwdRole& w = a.role[li];
             y.n = t.n[l];
             a.soff[li] = net->st_off[l];
             // projections into the layer, in projection order
@@ -1103,11 +1104,11 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
                 y.in_S[y.nin] = t.Sp[p];
                 y.in_ring_lds[y.nin] = t.fring[p];
                 y.in_ring[y.nin] = net->fring[p];
-                if (pre != 0) ++y.nrec;
+                if (pre != 0) ++w.nrec;
                 if (pre != 0) {
-                    y.in_ws[y.nin] = net->ws + t.woff[p];
-                    y.in_post[y.nin] = net->post + net->poff[p] * kPostCap;
-                    y.in_pcnt[y.nin] = net->pcnt + net->poff[p];
+                    w.in_ws[y.nin] = net->ws + t.woff[p];
+                    w.in_post[y.nin] = net->post + net->poff[p] * kPostCap;
+                    w.in_pcnt[y.nin] = net->pcnt + net->poff[p];
                     // position of p among the LIF-post projections of its source layer
                     int k = 0;
                     for (int p2 = 0; p2 < p; ++p2)
@@ -1126,9 +1127,9 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
                 y.ring_lds[y.npost] = t.fring[p];
                 y.ring[y.npost] = net->fring[p];
                 y.ws[y.npost] = net->ws + t.woff[p];
-                y.ffar[y.npost] = net->ffar + net->foff[p];
-                y.post[y.npost] = net->post + net->poff[p] * kPostCap;
-                y.pcnt[y.npost] = net->pcnt + net->poff[p];
+                w.ffar[y.npost] = net->ffar + net->foff[p];
+                w.post[y.npost] = net->post + net->poff[p] * kPostCap;
+                w.pcnt[y.npost] = net->pcnt + net->poff[p];
                 ++y.npost;
             }
             for (int k = y.npost; k < 2; ++k) {
@@ -1150,7 +1151,7 @@ extern "C" int snn_forward(snn_net* net, const snn_spikes_in* in, const float* c
             y.rec_idx = net->rec_idx + li * B * (size_t)(t.T + 1);
             y.rec_cnt = net->rec_cnt + li * B;
             y.steptab = net->steptab ? net->steptab + li * B * (size_t)t.T * SNN_STEP_ROW : nullptr;
-            y.masks = net->masks ? net->masks + li * B * (size_t)t.T * (net->core_threads / 64) : nullptr;
+            w.masks = net->masks ? net->masks + li * B * (size_t)t.T * (net->core_threads / 64) : nullptr;
             y.ncount = net->reg_on ? net->ncount + t.lif_off[l] : nullptr;
             y.out_count = records[li].count;
             y.out_step = records[li].step;

@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(1024) forward_ff_kernel(CoreFwdArgs a) {
         lds_u64* mk = (lds_u64*)smem + ((n0 / kFfBlock) & 1) * NW * kFfBlock;
         if (lane < kFfBlock) {
             mk[wave * kFfBlock + lane] = mine;
-            if (n0 + lane < T) y.masks[((size_t)b * T + n0 + lane) * NW + wave] = mine;
+            if (n0 + lane < T) a.role[0].masks[((size_t)b * T + n0 + lane) * NW + wave] = mine;
         }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0): LDS only

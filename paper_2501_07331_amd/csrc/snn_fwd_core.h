@@ -636,13 +636,13 @@ struct FwdCore {
         lds_f32* col = (lds_f32*)(reinterpret_cast<float*>(smem) + y.ring_lds[pp]) + lane;
         unsigned nw[kPostCap];                           // weight bits (0 past the list)
         int at[kPostCap];                                // byte offset of the neuron's mask word << 5, its bit
-        int most = live ? y.pcnt[pp][j] : 0;
+        int most = live ? a.role[l].pcnt[pp][j] : 0;
         {
             const int cnt = most;
 #pragma unroll
             for (int u = 0; u < kPostCap; ++u) {
                 uint2 v = make_uint2(0u, 0u);
-                if (u < cnt) v = y.post[pp][(size_t)j * kPostCap + u];
+                if (u < cnt) v = a.role[l].post[pp][(size_t)j * kPostCap + u];
                 nw[u] = v.x;
                 at[u] = (int)(((v.y & 0xFFFFu) >> 5) * 4) << 5 | (int)(v.y & 31u);
             }

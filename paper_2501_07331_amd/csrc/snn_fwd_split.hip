@@ -253,14 +253,14 @@ struct FwdSplit {
     static __device__ __forceinline__ void near_regs(const CoreFwdArgs& a, int j, int l, int e, int x, Lane& L) {
         const FwdLayer& y = a.ly[l];
         const bool live = j < y.n;
-        const int jc = min(j, y.n - 1), cnt = live ? y.in_pcnt[e][jc] : 0;
+        const int jc = min(j, y.n - 1), cnt = live ? a.role[l].in_pcnt[e][jc] : 0;
         int most = cnt;
 #pragma unroll
         for (int d = 32; d; d >>= 1) most = max(most, __shfl_xor(most, d, 64));
         L.most[l][x] = __builtin_amdgcn_readfirstlane(most);
 #pragma unroll
         for (int u = 0; u < EN; ++u) {
-            const uint2 v = y.in_post[e][(size_t)jc * kPostCap + u];
+            const uint2 v = a.role[l].in_post[e][(size_t)jc * kPostCap + u];
             const bool in = u < cnt;
             const int i = in ? (int)(v.y & 0xFFFFu) : 0;
             L.nw[l][x][u] = in ? v.x : 0u;
@@ -289,10 +289,10 @@ struct FwdSplit {
         }
         if (L.most[l][x] > EN) {
             const FwdLayer& y = a.ly[l];
-            const int jc = min(j, y.n - 1), cnt = j < y.n ? y.in_pcnt[e][jc] : 0;
+            const int jc = min(j, y.n - 1), cnt = j < y.n ? a.role[l].in_pcnt[e][jc] : 0;
 #pragma unroll 1
             for (int u = EN; u < cnt; ++u) {
-                const uint2 q = y.in_post[e][(size_t)jc * kPostCap + u];
+                const uint2 q = a.role[l].in_post[e][(size_t)jc * kPostCap + u];
                 const unsigned w = *(const lds_u32*)(smem + par * MASKS + near_at(y.in_l[e], q.y));
                 v = __fadd_rn(v, (w >> (q.y & 31)) & 1u ? __uint_as_float(q.x) : 0.0f);
             }
@@ -348,7 +348,7 @@ struct FwdSplit {
         // batch 128; with two layers, which have none left, 264 against 285,
         // 4-200-3 with a spiking output, T = 600, batch 256)
         const int npre = NL == 1 ? nq : a.ly[sl].n;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)y.in_ws[e], (short)0, npre * nq * 8,
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.role[l].in_ws[e], (short)0, npre * nq * 8,
                                                                             0x00020000);
         const Spikes last = H.s;
         uint2 w[HR];
@@ -410,7 +410,7 @@ struct FwdSplit {
                 any[l] |= ((const lds_u64*)(smem + CNT0 + par * CNTS + l * NWM * 2))[k];
 #pragma unroll
             for (int q = 0; q < NP; ++q) {
-                if (q >= a.ly[l].nrec) continue;
+                if (q >= a.role[l].nrec) continue;
                 lds_f32* c = (lds_f32*)(smem + L.cell[l][q]);
                 x[l][q] = *c;
                 *c = 0.0f;
@@ -428,7 +428,7 @@ struct FwdSplit {
             if (l == 0) L.I[0] = __fadd_rn(L.I[0], ain);     // layer 1's first projection is the inputs'
 #pragma unroll
             for (int q = 0; q < NP; ++q) {
-                if (q >= y.nrec) continue;
+                if (q >= a.role[l].nrec) continue;
                 const int e = q + (l == 0);
                 // the source layer: l itself, or l - 1 (a feed-forward projection)
                 const bool prev = l > 0 && y.in_l[e] != l;
@@ -459,7 +459,7 @@ struct FwdSplit {
 #pragma unroll
             for (int q = 0; q < NP; ++q) {
                 L.most[l][q] = 0;
-                if (q >= y.nrec) continue;
+                if (q >= a.role[l].nrec) continue;
                 const int e = q + (l == 0), row = y.n * 4;
                 // (lanes past the layer: the dummy row's first cell, never read)
                 L.row[l][q] = j < y.n ? row : 0;
@@ -632,7 +632,7 @@ struct FwdSplit {
                 if (pp >= a.ly[m].npost) continue;
                 const int nb = (a.ly[m].nq[pp] + 63) / 64;
                 if (t >= 0 && t < nb) {
-                    far = a.ly[m].ffar[pp];
+                    far = a.role[m].ffar[pp];
                     l = m;
                     npre = a.ly[m].npre[pp];
                     nq = a.ly[m].nq[pp];
@@ -712,7 +712,7 @@ struct FwdSplit {
                         y.rec_idx[(size_t)b * (T + 1) + n0 + lane] = idx[l];
 #pragma unroll
                         for (int k = 0; k < NWM; ++k)
-                            if (k < a.NW && y.masks) y.masks[((size_t)b * T + n0 + lane) * a.NW + k] = mk[l][k];
+                            if (k < a.NW && a.role[l].masks) a.role[l].masks[((size_t)b * T + n0 + lane) * a.NW + k] = mk[l][k];
                     }
                 }
 #pragma unroll
@@ -838,7 +838,7 @@ hipError_t launch_forward_split(const CoreFwdArgs& a, int n_lif, int np, size_t 
     const int waves = a.NW + a.NS + 1 + (a.ro_C > 0 ? 1 : 0);
     int ns = 0;
     for (int l = 0; l < n_lif; ++l) {
-        if (a.ly[l].npost > np || a.ly[l].nrec > np || a.ly[l].n > 64 * a.NW) return hipErrorInvalidValue;
+        if (a.ly[l].npost > np || a.role[l].nrec > np || a.ly[l].n > 64 * a.NW) return hipErrorInvalidValue;
         for (int pp = 0; pp < a.ly[l].npost; ++pp) {
             if (a.ly[l].ring_lds[pp] * 4 < f.head) return hipErrorInvalidValue;
             ns += (a.ly[l].nq[pp] + 63) / 64;

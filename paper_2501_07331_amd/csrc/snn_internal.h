@@ -104,10 +104,6 @@ struct FwdLayer {
     int in_S[2];                       //   LIF sources: that projection's ring slots,
     int in_ring_lds[2];                //   its ring (LDS float offset, or the HBM ring
     float* in_ring[2];                 //   [B][S+1][n])
-    int nrec;                          // how many are LIF-sourced (layer 0's first is the inputs')
-    const uint2* in_ws[2];             // split core, LIF sources: (weight bits, slot) [n_pre][n],
-    const uint2* in_post[2];           //   the posts' near synapses [n][kPostCap]
-    const int* in_pcnt[2];             //   and their number [n] (split_tables_kernel)
     int npost;                         // LIF-post projections out of the layer (recurrent, then
                                        // feed-forward); entries past npost repeat a valid one
     int nq[2];                         //   post neurons
@@ -116,21 +112,34 @@ struct FwdLayer {
     int ring_lds[2];                   //   delay ring [S+1][nq] (row S: dummy): LDS float offset,
     float* ring[2];                    //   or the HBM ring [B][S+1][nq]
     const uint2* ws[2];                //   (weight bits, slot) [n][nq]
-    const uint2* post[2];              //   cluster mode: the posts' near synapses [nq][kPostCap]
-    const int* pcnt[2];                //   and their number [nq] (split_tables_kernel)
-    const uint2* ffar[2];              //   split core: far table [n+1][nq] (split_tables_kernel)
     int* rec_n;                        // [B][cap] records: neuron, step, I-
     int* rec_s;
     float* rec_I;
     int* rec_idx;                      // [B][T+1] first record of each step
     int* rec_cnt;                      // [B]
     int* steptab;                      // [B][T][SNN_STEP_ROW], or NULL (split core only)
-    unsigned long long* masks;         // split, feed-forward cores: [B][T][NW] spikes of each 64
-                                       // neurons, one bit each
     int* ncount;                       // [n] spikes per neuron over the batch (added), or NULL
     int* out_count;                    // caller's records: [B], [B][cap], [B][cap]
     int* out_step;
     int* out_neuron;
+};
+
+// The same layer for the split, feed-forward and cluster cores.  (Apart from what
+// the general core reads: with fields of theirs among its own its argument loads
+// fell apart, two recurrent layers of 128, T = 500, batch 128, 1245 us against
+// 1208.)
+struct FwdRole {
+    int nrec;                          // how many projections into the layer are LIF-sourced
+                                       // (layer 0's first is the inputs')
+    const uint2* ffar[2];              // split core: far table [n+1][nq] (split_tables_kernel)
+    unsigned long long* masks;         // split, feed-forward cores: [B][T][NW] spikes of each 64
+                                       // neurons, one bit each
+    const uint2* in_post[2];           // split core, LIF sources: the posts' near synapses
+                                       //   [n][kPostCap]
+    const int* in_pcnt[2];             //   and their number [n] (split_tables_kernel),
+    const uint2* in_ws[2];             //   (weight bits, slot) [n_pre][n]
+    const uint2* post[2];              // cluster mode: the posts' near synapses [nq][kPostCap]
+    const int* pcnt[2];                //   and their number [nq] (split_tables_kernel)
 };
 
 struct CoreFwdArgs {
@@ -150,11 +159,13 @@ struct CoreFwdArgs {
     int ro_C, ro_feed, ro_nfeed, ro_S, ro_off, ro_loss;
     float ro_scale;
     const uint2* ro_ws;                // readout projection (weight bits, slot) [ro_nfeed][ro_C]
-    const uint2* ro_far;               // split core: its table [ro_nfeed + 1][ro_C] (split_tables_kernel)
     float* z;                          // [B][C]
     int* nstar;                        // [B][C]
-    int NS, ro_end;                    // split core: scatter waves, end of its LDS (bytes)
     ClusterArgs cl;                    // cluster mode (cl.G > 0): every ring in LDS, row width 64
+    int NS, ro_end;                    // split core: scatter waves, end of its LDS (bytes)
+    FwdRole role[SNN_MAX_LIF];
+    const uint2* ro_far;               // split core: the readout's table [ro_nfeed + 1][ro_C]
+                                       // (split_tables_kernel)
 };
 
 // Synapses that the split cores keep out of the rings: of slot 0 from a neuron
