@@ -203,7 +203,8 @@ static int scan_segments(int T, int S, int waves, size_t lds, int n_cu) {
 //             300          344 665 1000 1289       732 1405 2078 2773
 //             4-200-3      248 433 646 860         536 648 769 1279
 // (recurrent layers with their readouts, delays up to 25, 25, 30 and 40; dense: up
-// to 2; 4-200-3 with a spiking output, T = 600.)
+// to 2; 4-200-3 with a spiking output, T = 600.  The split backward core takes
+// about a twentieth less since.)
 static double general_time(long long k, int per_cu, int nw) {
     const double more = 0.04 + 0.055 * nw;
     auto round = [&](long long m) { return m > 0 ? 1.0 + (double)(m - 1) * more : 0.0; };

@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(1024) validate_kernel(const int* off, const in
 
 // The status block into host memory (mapped): a launch instead of a copy.
 __global__ void publish_status_kernel(const DevStatus* st, DevStatus* host) {
-    static_assert(sizeof(DevStatus) % 4 == 0, "copied as words");
+    static_assert(sizeof(DevStatus) % 4 == 0 && sizeof(DevStatus) <= 64 * 4, "copied as words, one a thread");
     const int i = threadIdx.x;
     if (i < (int)(sizeof(DevStatus) / 4)) reinterpret_cast<int*>(host)[i] = reinterpret_cast<const int*>(st)[i];
 }
@@ -114,11 +114,27 @@ __global__ void round_delays_kernel(RoundArgs a, uint8_t* slot, uint2* ws, DevSt
 
 // ------------------------------------------------------------------ input scan
 
+// Adds wv[q] to the cells at byte offset at[q] of the lane's column, in order, in
+// rounds of two (see column_add_rounds).
+__device__ __forceinline__ void ring_add(lds_f32* col, const int (&at)[KB], const float (&wv)[KB]) {
+    typedef __attribute__((address_space(3))) char lds_char;
+    auto cell = [&](int k) { return (lds_f32*)((lds_char*)col + at[k]); };
+#pragma unroll
+    for (int h = 0; h < KB; h += 2) {
+        const float v0 = *cell(h), v1 = *cell(h + 1);
+        const float s0 = __fadd_rn(v0, wv[h]);
+        const float s1 = __fadd_rn(at[h] == at[h + 1] ? s0 : v1, wv[h + 1]);
+        *cell(h) = s0;
+        *cell(h + 1) = s1;
+    }
+}
+
 // Workgroup = (sample b, block of 64 posts of layer 1, segment of steps), one
 // wave; lane j owns post j and the arrivals of steps [m0, m1) of the segment.
 // The events that can arrive there (emitted from S - 1 steps before the segment
-// on) stream by once, in emission order, in chunks of KB = 8, and each chunk's weights are added into an LDS ring of
-// R = S + TB - 1 arrival steps (row m % R; row R: dummy).  Rows of steps
+// on) stream by once, in emission order, in chunks of KB = 8, and each chunk's
+// weights are added into an LDS ring of R = S + TB - 1 arrival steps (row m % R;
+// row R: dummy).  Rows of steps
 // before the first emission step of the next chunk are final (every later
 // event arrives at its emission step or after): they go out as A_in rows and
 // are cleared, at most two per chunk on the common path.  A chunk whose
@@ -142,21 +158,6 @@ __global__ void round_delays_kernel(RoundArgs a, uint8_t* slot, uint2* ws, DevSt
 // the waves of a CU, so where the samples alone leave CUs idle a trial is cut
 // into segments, at the price of S - 1 steps of events read twice per cut (the
 // host weighs the two: scan_segments).
-// Adds wv[q] to the cells at byte offset at[q] of the lane's column, in order, in
-// rounds of two (see column_add_rounds).
-__device__ __forceinline__ void ring_add(lds_f32* col, const int (&at)[KB], const float (&wv)[KB]) {
-    typedef __attribute__((address_space(3))) char lds_char;
-    auto cell = [&](int k) { return (lds_f32*)((lds_char*)col + at[k]); };
-#pragma unroll
-    for (int h = 0; h < KB; h += 2) {
-        const float v0 = *cell(h), v1 = *cell(h + 1);
-        const float s0 = __fadd_rn(v0, wv[h]);
-        const float s1 = __fadd_rn(at[h] == at[h + 1] ? s0 : v1, wv[h + 1]);
-        *cell(h) = s0;
-        *cell(h + 1) = s1;
-    }
-}
-
 __global__ void __launch_bounds__(64) input_scan_kernel(InScanArgs a) {
     if (a.st->bad_input) return;
     const int n1 = a.n1, T = a.T, TB = a.TB, R = a.S + a.TB - 1;

@@ -1,9 +1,10 @@
 // The general LIF forward core of libsnn (gfx950, wave64): rings in device
-// memory, cluster mode, three or more LIF layers, layers wider than the split
-// core's waves (the others: snn_fwd_split.hip, snn_ff_core.hip).  A template; its
-// instantiations for 256 and 1024 threads live in two sources so that they
-// compile in parallel.  One workgroup per sample runs the LIF layers over T steps (Table 1, forward dynamics with delayed
-// current jumps).  Lane j owns neuron j of every LIF layer and column j of
+// memory, cluster mode, two layers of which one is recurrent, three or more,
+// layers wider than the split core's waves, and batches of several samples a CU
+// where it is the faster one (the others: snn_fwd_split.hip, snn_ff_core.hip).  A
+// template; its instantiations for 256 and 1024 threads live in two sources so
+// that they compile in parallel.  One workgroup per sample runs the LIF layers
+// over T steps (Table 1, forward dynamics with delayed current jumps).  Lane j owns neuron j of every LIF layer and column j of
 // every delay ring into that layer.
 //
 // Per step n: free dynamics, threshold and reset, wave ballots into LDS, a

@@ -57,17 +57,19 @@ __device__ __forceinline__ void lds_barrier() {
 // Tables of the LIF -> LIF projections, from their (weight, slot) pairs.
 //  workgroups [0, rowblocks): one wave per neuron i of the LIF layers: its
 //      rows of the far tables: of the backward core (far: weight bits, far_entry),
-//      of the forward core (ffar [n + 1][nq]: weight
-//      bits, slot times the bytes of a ring row) with slots 0 and 1 as weight +0
-//      at the largest slot (a cell that no pending step reads; a readout's
-//      table has all slots); row n of ffar, which stands in for spikes past a
-//      chunk's end, likewise; and its synapses of slot 0 for the backward core, projections then posts
-//      in order: the first kNearCap (weight bits; LDS byte offset of the post's
-//      fp64 ring column, projection << 16) and their number.
+//      of the forward core (ffar [n + 1][nq]: weight bits, slot times the bytes of
+//      a ring row) with slots 0 and 1 as weight +0 at the largest slot (a cell
+//      that no pending step reads; a readout's table has all slots); row n of
+//      ffar, which stands in for spikes past a chunk's end, likewise; and its
+//      synapses of slot 0 for the backward core, projections then posts in order:
+//      the first kNearCap (weight bits; LDS byte offset of the post's fp64 ring
+//      column, projection << 16) and their number.
 //  the others: 64 posts of a projection each: the posts' synapses of slot 1
-//      (where post_slots is 2), then slot 0, each in presynaptic order: the first kPostCap (weight bits;
-//      neuron, slot << 16) and their number.
-// The largest numbers go to the status block.
+//      (where post_slots is 2), then slot 0, each in presynaptic order: the first
+//      kPostCap (weight bits; neuron, slot << 16) and their number.
+// The largest numbers go to the status block.  (One launch for both directions in
+// every forward: whether a backward follows is not known there, and weights and
+// delays may have changed when it comes.)
 __global__ void __launch_bounds__(512) split_tables_kernel(SplitTables a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (a.st->bad_input) return;
@@ -188,9 +190,9 @@ struct FwdSplit {
     }
     static_assert(EN + (EN < 24 ? 8 : 4) <= kPostCap, "the lists hold them");
     static constexpr int U = 2 * D;                  // steps that input arrivals are loaded ahead
-    // spikes of a step whose rows are loaded a step ahead (as the registers allow)
     static constexpr int kRound = 2;                 // ring cells read together (see cells_add)
     static constexpr int KG = 4;                     // spikes whose rows are loaded and added together
+    // spikes of a step whose rows are loaded a step ahead (as the registers allow)
     static constexpr int PK = NL == 1 && NWM == 4 ? 16 : 8;
 
     // The spikes of a layer at a step (uniform): how many, and how many before

@@ -117,7 +117,7 @@ struct FwdLayer {
     float* rec_I;
     int* rec_idx;                      // [B][T+1] first record of each step
     int* rec_cnt;                      // [B]
-    int* steptab;                      // [B][T][SNN_STEP_ROW], or NULL (split core only)
+    int* steptab;                      // [B][T][SNN_STEP_ROW], or NULL (split, feed-forward cores)
     int* ncount;                       // [n] spikes per neuron over the batch (added), or NULL
     int* out_count;                    // caller's records: [B], [B][cap], [B][cap]
     int* out_step;
