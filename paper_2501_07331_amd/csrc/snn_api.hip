@@ -523,6 +523,19 @@ extern "C" int snn_create(const snn_layer* layers, int32_t n_layers, float tau_m
                 const double one = nwaves > 4 ? 0.5 + 0.13 * (nwaves - 5) : (t.n_lif == 1 ? 0.5 : 0.36) + 0.08 * ns;
                 faster = (double)((k + per - 1) / per) * one <= general_time(k, gper, nwaves);
             }
+            // (and unless more than half the CUs have a sample and the delays of a
+            // layer of 193 to 256 neurons are so short that, drawn evenly from
+            // them, some neuron has more near synapses than a list holds, with a
+            // mean 1.5 n / d above 20.5: the neuron waves' rows beside the scatter
+            // waves' then cost what the split saves, 700-256-20, T = 1000, batch
+            // 256: delays up to 5 1122 us, to 14 1163, the general core 1058; T =
+            // 500, batch 128, up to 5 508 and 512)
+            if (fits && t.n_lif == 1 && nwaves == 4 && 2 * t.B > n_cu) {
+                int d = 0;
+                for (int p = 0; p < t.P; ++p)
+                    if (t.pre[p] == 1 && t.post[p] == 1) d = t.dmax[p];
+                if (3 * t.n[1] > 41 * std::max(d, 1)) faster = false;
+            }
             if (fits && faster) {
                 net->split_f = 1;
                 net->split_NS = ns;

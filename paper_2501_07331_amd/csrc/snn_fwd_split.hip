@@ -32,7 +32,8 @@
 // spikes instead, which they hold from one step to the next (dense_add: a step's
 // rows give its slot 0 at once and its slot 1 a step later).  T = 500, batch 128,
 // delays up to 5: 256 neurons 504 us, 128 362, 64 312 (both steps' rows loaded
-// in the step: 683, 481, 374; the general core 512, 405, 355).
+// in the step: 683, 481, 374; the general core 512, 405, 355; T = 1000, batch
+// 256: 1122 and 1057, left to the general core by the host).
 //
 // Measured, 700-256-20 recurrent, T = 1000: the core with the readout 1063 -> 792
 // us at batch 256, 1042 -> 772 us at 32; T = 4000 at a quarter of the time step,
@@ -40,8 +41,8 @@
 // -> 286 us.  Bound
 // by the ordered adds into the rings (without them 475 of 772 us; without the
 // readout wave 111 less).  Slot 0 alone kept near: 885; ring cells read four
-// together instead of two: 804 against 780; lists of 16 instead of 24 registers
-// 2549 against 2010 (fine grid).
+// together instead of two: 804 against 780; lists of 16 instead of 24 or 32
+// registers 2549 against 2010 (fine grid).
 #include "snn_bwd_plan.h"
 #include "snn_device.h"
 
@@ -174,21 +175,20 @@ struct FwdSplit {
     static constexpr int MASKS = NL * NWM * 8, CNTS = NL * NWM * 2, LIST = NL * NWM * 64;
     static constexpr int CNT0 = 0, MASK0 = (CNT0 + D * CNTS + 15) / 16 * 16, LIST0 = MASK0 + (D + 1) * MASKS,
                          CUR0 = LIST0 + D * LIST * 2, HEAD = CUR0 + D * LIST * 4;
-    // near synapses a lane holds in registers (the rest would be read from
-    // memory in every step with spikes: delays drawn from 0 .. 50 give a neuron
-    // 7.7 of them among 256, and the most of 256 neurons about 17)
-    static constexpr int EN = NL == 1 && NWM == 4 ? 24 : 16;
-    // The longest lists taken synapse by synapse, with nw neuron waves: an entry
-    // past the registers costs a memory access in every step with spikes, the
-    // dense form one for every spike, and narrow layers have few.  T = 500, batch
-    // 128, recurrent layers, list against dense form: 64 neurons, lists of 31,
-    // 374 and 312 us; 128, 30, 381 and 359; 256, 31, 464 and 508; 300 (16
-    // registers), 26, 808 and 670, 20, 548 and 665.
-    // (Two layers of 100 and 60, 21 to 24: 432 and 444.)
+    // near synapses a lane holds in registers (the rest is read from memory in
+    // every step with spikes: delays drawn from 0 .. 50 give a neuron 7.7 of them
+    // among 256, and the most of 256 neurons about 17)
+    static constexpr int EN = NL == 1 && NWM == 4 ? kPostCap : 16;
+    // The longest lists taken synapse by synapse, with nw neuron waves; longer
+    // ones in the dense form.  T = 500, batch 128, list and dense form: one layer
+    // of 64, lists of 31, 212 and 312 us, of 128 (30) 244 and 362, of 256 (31) 379
+    // and 508 (with 24 registers 374, 381, 464: a memory access an entry and step);
+    // of 300 (16 registers), 20: 548 and 665, 26: 808 and 670, T = 2000 2320 and
+    // 1647; two layers of 100 and 60, 21 to 24: 428 and 444; of 256 each, 25 to
+    // 30: 773 and 860.
     static __device__ __forceinline__ int near_limit(int nw) {
-        return nw <= 2 ? (NL == 1 ? EN + 4 : EN + 8) : nw <= 4 ? kPostCap : EN + 8;
+        return NL == 1 ? (nw <= 4 ? kPostCap : EN + 8) : nw <= 2 ? EN + 8 : kPostCap;
     }
-    static_assert(EN + (EN < 24 ? 8 : 4) <= kPostCap, "the lists hold them");
     static constexpr int U = 2 * D;                  // steps that input arrivals are loaded ahead
     static constexpr int kRound = 2;                 // ring cells read together (see cells_add)
     static constexpr int KG = 4;                     // spikes whose rows are loaded and added together
@@ -289,14 +289,39 @@ struct FwdSplit {
                 v = __fadd_rn(v, __uint_as_float(s & L.nw[l][x][u0 + u]));
             }
         }
-        if (L.most[l][x] > EN) {
+        // the rest of the list: four entries' loads together, with two layers (no
+        // registers left: 275 us against 266, 4-200-3 with a spiking output) one
+        if constexpr (NL > 1) {
+            if (L.most[l][x] > EN) {
+                const FwdLayer& y = a.ly[l];
+                const int jc = min(j, y.n - 1), cnt = j < y.n ? a.role[l].in_pcnt[e][jc] : 0;
+#pragma unroll 1
+                for (int u = EN; u < cnt; ++u) {
+                    const uint2 q = a.role[l].in_post[e][(size_t)jc * kPostCap + u];
+                    const unsigned w = *(const lds_u32*)(smem + par * MASKS + near_at(y.in_l[e], q.y));
+                    v = __fadd_rn(v, (w >> (q.y & 31)) & 1u ? __uint_as_float(q.x) : 0.0f);
+                }
+            }
+        } else if constexpr (EN < kPostCap) {
+            constexpr int TG = 4;
             const FwdLayer& y = a.ly[l];
             const int jc = min(j, y.n - 1), cnt = j < y.n ? a.role[l].in_pcnt[e][jc] : 0;
 #pragma unroll 1
-            for (int u = EN; u < cnt; ++u) {
-                const uint2 q = a.role[l].in_post[e][(size_t)jc * kPostCap + u];
-                const unsigned w = *(const lds_u32*)(smem + par * MASKS + near_at(y.in_l[e], q.y));
-                v = __fadd_rn(v, (w >> (q.y & 31)) & 1u ? __uint_as_float(q.x) : 0.0f);
+            for (int u0 = EN; u0 < L.most[l][x]; u0 += TG) {
+                uint2 q[TG];
+                unsigned w[TG];
+#pragma unroll
+                for (int u = 0; u < TG; ++u) {
+                    q[u] = a.role[l].in_post[e][(size_t)jc * kPostCap + u0 + u];
+                    if (u0 + u >= cnt) q[u] = make_uint2(0u, 0u);
+                }
+#pragma unroll
+                for (int u = 0; u < TG; ++u) w[u] = *(const lds_u32*)(smem + par * MASKS + near_at(y.in_l[e], q[u].y));
+#pragma unroll
+                for (int u = 0; u < TG; ++u) {
+                    const unsigned k = (unsigned)__builtin_amdgcn_sbfe((int)w[u], (int)(q[u].y & 31u), 1);
+                    v = __fadd_rn(v, __uint_as_float(k & q[u].x));
+                }
             }
         }
         return v;
@@ -304,24 +329,24 @@ struct FwdSplit {
 
     // The rows of a step's first HR spikes that a lane holds of one projection:
     // the step's slot 0 is added from them, a step later its slot 1.
-    static constexpr int HR = NL == 1 ? 16 : 8;
+    static constexpr int HR = NL == 1 ? 16 : 8, DG = NL == 1 ? KG : KB;   // (DG: loaded together)
     struct Held {
         Spikes s;
         uint2 w[HR];
     };
 
-    // Rows r0 .. r0 + KB (of the lane's ids; past the spikes: loaded, not used).
+    // Rows r0 .. r0 + DG (of the lane's ids; past the spikes: loaded, not used).
     static __device__ __forceinline__ void dense_load(__amdgpu_buffer_rsrc_t rs, int col8, int row8, int ids, int r0,
                                                       uint2* w) {
 #pragma unroll
-        for (int k = 0; k < KB; ++k) {
+        for (int k = 0; k < DG; ++k) {
             const auto v = __builtin_amdgcn_raw_buffer_load_b64(rs, col8, __builtin_amdgcn_readlane(ids, r0 + k) * row8, 0);
             w[k] = make_uint2((unsigned)v[0], (unsigned)v[1]);
         }
     }
     static __device__ __forceinline__ float dense_sum(const uint2* w, int left, unsigned slot, float v) {
 #pragma unroll
-        for (int k = 0; k < KB; ++k)
+        for (int k = 0; k < DG; ++k)
             v = __fadd_rn(v, k < left && w[k].y == slot ? __uint_as_float(w[k].x) : 0.0f);
         return v;
     }
@@ -330,8 +355,8 @@ struct FwdSplit {
     static __device__ __forceinline__ float dense_rest(__amdgpu_buffer_rsrc_t rs, int col8, int row8, const Spikes& s,
                                                        int n, int sl, unsigned slot, float v) {
 #pragma unroll 1
-        for (int r0 = HR; r0 < s.total; r0 += KB) {
-            uint2 x[KB];
+        for (int r0 = HR; r0 < s.total; r0 += DG) {
+            uint2 x[DG];
             dense_load(rs, col8, row8, list_ids(s, n, sl, r0, 0), 0, x);
             v = dense_sum(x, s.total - r0, slot, v);
         }
@@ -360,15 +385,15 @@ struct FwdSplit {
         if (H.s.total > 0) {
             const int ids = list_ids(H.s, n, sl, 0, 0);
 #pragma unroll
-            for (int g = 0; g < HR; g += KB)
+            for (int g = 0; g < HR; g += DG)
                 if (g == 0 || H.s.total > g) dense_load(rs, col8, nq * 8, ids, g, H.w + g);
         }
 #pragma unroll
-        for (int g = 0; g < HR; g += KB)
+        for (int g = 0; g < HR; g += DG)
             if (last.total > g) v = dense_sum(w + g, last.total - g, 1u, v);
         if (last.total > HR) v = dense_rest(rs, col8, nq * 8, last, n - 1, sl, 1u, v);
 #pragma unroll
-        for (int g = 0; g < HR; g += KB)
+        for (int g = 0; g < HR; g += DG)
             if (H.s.total > g) v = dense_sum(H.w + g, H.s.total - g, 0u, v);
         if (H.s.total > HR) v = dense_rest(rs, col8, nq * 8, H.s, n, sl, 0u, v);
         return v;

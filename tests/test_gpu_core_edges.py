@@ -107,11 +107,12 @@ def test_one_neuron_with_a_list_at_its_limits(widths, near):
 @pytest.mark.parametrize("layers,B,high", [
     (_lif(33), 1300, 6.0), (_lif(130), 520, 6.0), (_lif(256), 520, 1.0), (_lif(70), 1030, 6.0),
     (_lif(33, 40), 1030, 6.0), (((N_IN, 0, 0), (70, 1, 0), (3, 1, 0)), 1030, 6.0), (_lif(300), 520, 1.0),
-    (_lif(512), 3, 1.0), (_lif(512), 3, 20.0)])
+    (_lif(512), 3, 1.0), (_lif(512), 3, 20.0), (_lif(200), 140, 1.0), (_lif(200), 140, 15.0)])
 def test_batches_of_several_samples_a_cu(layers, B, high):
     """More samples than compute units, where the general cores take over from the
     split ones one after the other, and the widest layer that the split backward
-    core serves with its slot-0 synapses in the lists and past them."""
+    core serves with its slot-0 synapses in the lists and past them; a layer with
+    short delays, on more than half the units, to either side of its rule."""
     loss = LOSS_DMSE if layers[-1][1] == 1 else None
     _check(_net(layers, 24, B, high, d_in=3, drive=1.0, rate=0.1, loss=loss), least=0.2)
 
