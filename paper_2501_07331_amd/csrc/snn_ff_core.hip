@@ -30,6 +30,10 @@ __global__ void __launch_bounds__(1024) forward_ff_kernel(CoreFwdArgs a) {
     const bool live = tid < y.n;
     const size_t r0 = (size_t)b * cap;
     gptr<const float> ain = (gptr<const float>)(a.A_in + (size_t)b * T * a.n1 + min(tid, a.n1 - 1));
+    // this lane's mask word of the block at step 0 (in vector registers: as an
+    // argument it was loaded in every block, 90 us against 85)
+    gptr<unsigned long long> mrow = (gptr<unsigned long long>)(a.role[0].masks + ((size_t)b * T + lane) * NW + wave);
+    asm volatile("" : "+v"(mrow));
     float V = 0.0f, I = 0.0f;
     int own = 0, cnt = 0;
     float x[kFfBlock];
@@ -59,7 +63,7 @@ __global__ void __launch_bounds__(1024) forward_ff_kernel(CoreFwdArgs a) {
         lds_u64* mk = (lds_u64*)smem + ((n0 / kFfBlock) & 1) * NW * kFfBlock;
         if (lane < kFfBlock) {
             mk[wave * kFfBlock + lane] = mine;
-            if (n0 + lane < T) a.role[0].masks[((size_t)b * T + n0 + lane) * NW + wave] = mine;
+            if (n0 + lane < T) mrow[(size_t)n0 * NW] = mine;
         }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0): LDS only
